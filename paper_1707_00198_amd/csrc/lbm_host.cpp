@@ -529,8 +529,8 @@ int create_t(lbm_ctx *c, const lbm_domain_desc *d) {
         D.wetting = q.wetting;
         D.io_off = io;
         DomPar<double> &PD = D.d;
-        PD.inv2nu_r = 1.0 / (2.0 * q.nu_r);
-        PD.inv2nu_b = 1.0 / (2.0 * q.nu_b);
+        PD.inv_nu_sum = 1.0 / (2.0 * q.nu_r) + 1.0 / (2.0 * q.nu_b);
+        PD.inv_nu_diff = 1.0 / (2.0 * q.nu_r) - 1.0 / (2.0 * q.nu_b);
         PD.half_sigma = 0.5 * q.sigma;
         PD.beta = q.beta;
         PD.cos_t = std::cos(th);
@@ -544,7 +544,10 @@ int create_t(lbm_ctx *c, const lbm_domain_desc *d) {
         PD.rho0 = q.rho0;
         PD.eps = q.eps;
         PD.outlet_u = q.outlet_u;
-        PD.pad = 0.0;
+        PD.w_rest = WH[0] * q.rho0;
+        PD.w_axis = WH[1] * q.rho0;
+        PD.w_diag = WH[5] * q.rho0;
+        PD.pad[0] = PD.pad[1] = 0.0;
         const double *pd = &PD.rho0;
         float *pf = &D.f.rho0;
         for (size_t k = 0; k < sizeof(DomPar<double>) / sizeof(double); k++) pf[k] = (float)pd[k];

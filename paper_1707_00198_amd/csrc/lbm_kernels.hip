@@ -55,13 +55,13 @@ __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x);
 __device__ __forceinline__ double fsqrt(double x) { return sqrt(x); }
 __device__ __forceinline__ float fsqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
 
-// a / b: IEEE in FP64; in FP32 the 1-ulp reciprocal refined by one Newton step, which removes
+// a / b: IEEE in FP64; in FP32 the 1-ulp reciprocal ib refined by one Newton step, which removes
 // the reciprocal's systematic bias (the red fraction c = rho_R / rho must not drift the
 // colour masses).
-__device__ __forceinline__ double quotient(double a, double b) { return a / b; }
-__device__ __forceinline__ float quotient(float a, float b) {
-    const float q = a * rcp(b);
-    return fmaf(rcp(b), fmaf(-q, b, a), q);
+__device__ __forceinline__ double quotient(double a, double b, double) { return a / b; }
+__device__ __forceinline__ float quotient(float a, float b, float ib) {
+    const float q = a * ib;
+    return fmaf(ib, fmaf(-q, b, a), q);
 }
 
 // Colour indicator (Eq. 12), exactly +-1 in pure phases.
@@ -70,27 +70,155 @@ __device__ __forceinline__ float colour_indicator(float rR, float rB) {
     return rB == 0.0f ? 1.0f : (rR == 0.0f ? -1.0f : (rR - rB) * rcp(rR + rB));
 }
 
-// Unit interface normal (Eq. 22) from a gradient of modulus g > 0.
-__device__ __forceinline__ void unit_normal(double gx, double gy, double g, double &nx, double &ny) {
-    nx = gx / g;
-    ny = gy / g;
+// ------------------------------------------------------------- node arithmetic
+// The arithmetic of one node, shared by every step kernel.  Each function fixes which products
+// are fused into sums (contract(on): within one expression only), so that a node gets the same
+// bits from every kernel and tile shape, whatever the compiler could fuse around it.
+
+// Modulus g and unit normal (Eq. 22) of a gradient; n = 0 where g <= eps.  FP32: one
+// reciprocal square root gives both (g = 0 gives 0 * inf = NaN, which fails the test too).
+__device__ __forceinline__ void unit_normal(double gx, double gy, double eps, double &g, double &nx,
+                                            double &ny) {
+#pragma clang fp contract(on)
+    g = sqrt(gx * gx + gy * gy);
+    nx = g > eps ? gx / g : 0.0;
+    ny = g > eps ? gy / g : 0.0;
 }
-__device__ __forceinline__ void unit_normal(float gx, float gy, float g, float &nx, float &ny) {
-    const float ig = rcp(g);
-    nx = gx * ig;
-    ny = gy * ig;
+__device__ __forceinline__ void unit_normal(float gx, float gy, float eps, float &g, float &nx,
+                                            float &ny) {
+#pragma clang fp contract(on)
+    const float g2 = gx * gx + gy * gy;
+    const float ig = __builtin_amdgcn_rsqf(g2);
+    g = g2 * ig;
+    const bool on = g > eps;
+    g = on ? g : 0.0f;
+    nx = on ? gx * ig : 0.0f;
+    ny = on ? gy * ig : 0.0f;
 }
 
-// Accumulate s +/- w*v.  In FP64 the product is rounded before the sum (no contraction), as in
-// a plain IEEE evaluation: the colour gradient feeds branches (|grad| > eps, the contact-angle
-// selection) whose symmetric ties must round the same way.
-__device__ __forceinline__ double acc_nc(double s, double w, double v, int sign) {
+// Gradient of a field by the nine-point stencil (Eq. 28: 3 sum_a w_a e_a f), from the column
+// sums t = f(y)/3 + (f(y-1) + f(y+1))/12 of the two neighbour columns and the differences
+// u = f(y+1) - f(y-1) of all three: 13 operations instead of 24, and mirror-symmetric values
+// cancel exactly (n = 0 on the axis).
+template <class AT>
+__device__ __forceinline__ AT column_sum(AT lo, AT mid, AT hi) {
+#pragma clang fp contract(on)
+    const AT q = AT(1.0 / 3.0) * mid;
+    return AT(1.0 / 12.0) * (lo + hi) + q;
+}
+template <class AT>
+__device__ __forceinline__ AT row_sum(AT um, AT u0, AT up) {
+#pragma clang fp contract(on)
+    const AT q = AT(1.0 / 3.0) * u0;
+    return AT(1.0 / 12.0) * (um + up) + q;
+}
+template <class AT, class F>
+__device__ __forceinline__ void gradient(F f, AT &gx, AT &gy) {
+    const AT mm = f(-1, -1), m0 = f(-1, 0), mp = f(-1, 1);
+    const AT pm = f(1, -1), p0 = f(1, 0), pp = f(1, 1);
+    const AT zm = f(0, -1), zp = f(0, 1);
+    gx = column_sum(pm, p0, pp) - column_sum(mm, m0, mp);
+    gy = row_sum(mp - mm, zp - zm, pp - pm);
+}
+
+// The same gradient on an outermost fluid node, summed direction by direction like a plain
+// evaluation of Eq. 28 (in FP64 each product rounded before its sum): there its direction feeds
+// the contact-angle selection (Eq. 36), whose ties must round the same way.
+__device__ __forceinline__ double add_term(double s, double w, double v) {
 #pragma clang fp contract(off)
     const double t = w * v;
-    return sign > 0 ? s + t : s - t;
+    return s + t;
 }
-__device__ __forceinline__ float acc_nc(float s, float w, float v, int sign) {
-    return sign > 0 ? s + w * v : s - w * v;
+__device__ __forceinline__ float add_term(float s, float w, float v) { return fmaf(w, v, s); }
+template <class AT, class F>
+__device__ __forceinline__ void wall_gradient(F f, AT &gx, AT &gy) {
+    AT sx = AT(0), sy = AT(0);
+#pragma unroll
+    for (int a = 1; a < 9; a++) {
+        const AT v = f(EX[a], EY[a]);
+        if (EX[a]) sx = add_term(sx, AT(EX[a]) * wgt<AT>(a), v);
+        if (EY[a]) sy = add_term(sy, AT(EY[a]) * wgt<AT>(a), v);
+    }
+    gx = AT(3) * sx;
+    gy = AT(3) * sy;
+}
+
+// Virtual values of an outermost solid node (Eq. 29): the weighted mean of a field (or of two)
+// over the fluid neighbours, m being the node's class word.
+template <class AT, class F>
+__device__ __forceinline__ AT fluid_mean(uint32_t m, F f) {
+#pragma clang fp contract(on)
+    AT num = AT(0), den = AT(0);
+#pragma unroll
+    for (int a = 1; a < 9; a++) {
+        if (m & (1u << (a - 1))) continue;
+        num += wgt<AT>(a) * f(EX[a], EY[a]);
+        den += wgt<AT>(a);
+    }
+    return num * rcp(den);
+}
+template <class AT, class F>
+__device__ __forceinline__ void fluid_mean2(uint32_t m, F f, AT &x, AT &y) {
+#pragma clang fp contract(on)
+    AT nx = AT(0), ny = AT(0), den = AT(0);
+#pragma unroll
+    for (int a = 1; a < 9; a++) {
+        if (m & (1u << (a - 1))) continue;
+        AT vx, vy;
+        f(EX[a], EY[a], vx, vy);
+        nx += wgt<AT>(a) * vx;
+        ny += wgt<AT>(a) * vy;
+        den += wgt<AT>(a);
+    }
+    const AT iden = rcp(den);
+    x = nx * iden;
+    y = ny * iden;
+}
+
+// Eq. 48 on an outermost fluid node: weighted mean of the differences to the fluid neighbours.
+template <class AT, class F>
+__device__ __forceinline__ void one_sided_gradient(uint32_t m, F f, AT &dxnx, AT &dynx, AT &dxny,
+                                                   AT &dyny) {
+#pragma clang fp contract(on)
+    AT nx0, ny0, den = AT(0);
+    f(0, 0, nx0, ny0);
+    dxnx = dynx = dxny = dyny = AT(0);
+#pragma unroll
+    for (int a = 1; a < 9; a++) {
+        if (m & (1u << (a - 1))) continue;
+        AT vx, vy;
+        f(EX[a], EY[a], vx, vy);
+        vx = wgt<AT>(a) * (vx - nx0);
+        vy = wgt<AT>(a) * (vy - ny0);
+        if (EX[a]) {
+            dxnx += AT(EX[a]) * vx;
+            dxny += AT(EX[a]) * vy;
+        }
+        if (EY[a]) {
+            dynx += AT(EY[a]) * vx;
+            dyny += AT(EY[a]) * vy;
+        }
+        den += wgt<AT>(a);
+    }
+    const AT iden = rcp(den);
+    dxnx *= iden;
+    dynx *= iden;
+    dxny *= iden;
+    dyny *= iden;
+}
+
+// CSF force (Eqs. 10, 13) from the derivatives of n, with grad rho^N = g n.
+template <class AT>
+__device__ __forceinline__ void csf_force(AT half_sigma, AT g, AT nx, AT ny, AT dxnx, AT dynx, AT dxny,
+                                          AT dyny, AT &Fx, AT &Fy) {
+#pragma clang fp contract(on)
+    const AT a = nx * ny, b = ny * ny, c = nx * nx;
+    const AT s = dynx + dxny;
+    const AT t = a * s - b * dxnx;
+    const AT kappa = t - c * dyny;
+    const AT q = half_sigma * g * kappa;
+    Fx = q * nx;
+    Fy = q * ny;
 }
 
 // ------------------------------------------------------------------ storage codec
@@ -255,6 +383,20 @@ __device__ __forceinline__ bool pull_outside(const Nbr &n, int a) {
     return (n.lo && EX[a] == 1) || (n.hi && EX[a] == -1);
 }
 
+// Adds the population f that direction a pulls from a node of colour state (c, v) to the red
+// density (c f + w_a e_a . v, Eq. 14) and to the total.  The total takes the same steps as the
+// red density, so where every source is pure red (c = 1, v = 0) the two stay equal.
+template <class AT>
+__device__ __forceinline__ void add_pull(int a, AT f, AT c, AT vx, AT vy, AT &rR, AT &tot) {
+#pragma clang fp contract(on)
+    const AT ev = EX[a] == 0 ? (EY[a] > 0 ? vy : -vy)
+                             : (EY[a] == 0 ? (EX[a] > 0 ? vx : -vx)
+                                           : (EX[a] > 0 ? vx : -vx) + (EY[a] > 0 ? vy : -vy));
+    rR = c * f + rR;
+    rR = wgt<AT>(a) * ev + rR;
+    tot = tot + f;
+}
+
 // Completes the post-streaming populations d[] of fluid node (x, y) whose interior pulls are
 // already in d[] (and whose own-node snapshot values are in d[] in snapshot mode): half-way
 // bounce-back on links from solid nodes, Zou-He inlet and convective outlet unknowns; and
@@ -266,6 +408,7 @@ template <bool BOUNCED, class T, class AT, class ColourFn>
 __device__ __forceinline__ void finish_gather(const StepArgs<T, AT> &A, DomC &D, int x, int y,
                                               uint32_t m, const Nbr &nb, bool write_hist, AT d[9],
                                               AT &rR, AT &rB, ColourFn colour) {
+#pragma clang fp contract(on)
     const size_t self = nb.row[1] + x;
     ParC<AT> &P = par(D, AT());
     const AT rho0 = P.rho0;
@@ -273,43 +416,31 @@ __device__ __forceinline__ void finish_gather(const StepArgs<T, AT> &A, DomC &D,
     colour(0, cself, vxs, vys);
     rR = AT(0);
     rB = AT(0);
+    const AT wr[3] = {P.w_rest, P.w_axis, P.w_diag};
     if (A.own) {
         // node-local snapshot: every population carries the node's own red fraction
         AT tot = AT(0);
 #pragma unroll
-        for (int a = 0; a < 9; a++) tot += wgt<AT>(a) * rho0 + d[a];
+        for (int a = 0; a < 9; a++) tot += wr[(a + 3) >> 2] + d[a];
         rR = cself * tot;
         rB = tot - rR;
     } else if ((m & 0xFFu) == 0u && !nb.lo && !nb.hi) {
         // interior node: every population is pulled from a fluid neighbour
-        AT tot = wgt<AT>(0) * rho0 + d[0];
+        AT tot = wr[0] + d[0];
         rR = cself * tot;
 #pragma unroll
         for (int a = 1; a < 9; a++) {
             AT c, vx, vy;
             colour(a, c, vx, vy);
-            const AT fa = wgt<AT>(a) * rho0 + d[a];
-            rR += c * fa + wgt<AT>(a) * (AT(EX[a]) * vx + AT(EY[a]) * vy);
-            tot += fa;
+            add_pull(a, wr[a < 5 ? 1 : 2] + d[a], c, vx, vy, rR, tot);
         }
         rB = tot - rR;
     } else {
-        AT cs[9], vsx[9], vsy[9];
-        cs[0] = cself;
-        vsx[0] = vsy[0] = AT(0);
+        if (!BOUNCED) {
 #pragma unroll
-        for (int a = 1; a < 9; a++) {
-            if (pull_outside(nb, a)) {  // completed below
-                cs[a] = cself;
-                vsx[a] = vsy[a] = AT(0);
-            } else if (m & (1u << (OPP[a] - 1))) {  // half-way bounce-back
-                if (!BOUNCED) d[a] = Codec<T>::load(A.fin + OPP[a] * A.plane + self, OPP[a]);
-                cs[a] = cself;
-                vsx[a] = -vxs;
-                vsy[a] = -vys;
-            } else {
-                colour(a, cs[a], vsx[a], vsy[a]);
-            }
+            for (int a = 1; a < 9; a++)
+                if (!pull_outside(nb, a) && (m & (1u << (OPP[a] - 1))))  // half-way bounce-back
+                    d[a] = Codec<T>::load(A.fin + OPP[a] * A.plane + self, OPP[a]);
         }
         if (nb.lo) {
             // Zou-He velocity inlet on the total f; injected fluid is pure red.
@@ -319,7 +450,6 @@ __device__ __forceinline__ void finish_gather(const StepArgs<T, AT> &A, DomC &D,
             d[1] = d[3] + AT(2.0 / 3.0) * ru;
             d[5] = d[7] - AT(0.5) * (d[2] - d[4]) + AT(1.0 / 6.0) * ru;
             d[8] = d[6] + AT(0.5) * (d[2] - d[4]) + AT(1.0 / 6.0) * ru;
-            cs[1] = cs[5] = cs[8] = AT(1);
         }
         if (nb.hi) {
             // Convective outlet f_a <- [f_a(t) + U f_a(x - 1, t + 1)] / (1 + U), coloured with
@@ -345,12 +475,19 @@ __device__ __forceinline__ void finish_gather(const StepArgs<T, AT> &A, DomC &D,
         }
         // rho_B as the total minus rho_R: exactly 0 where every source is pure red (c = 1,
         // v = 0), and rho_R exactly 0 where every source is pure blue
-        AT tot = AT(0);
+        AT tot = wr[0] + d[0];
+        rR = cself * tot;
 #pragma unroll
-        for (int a = 0; a < 9; a++) {
-            const AT fa = wgt<AT>(a) * rho0 + d[a];
-            rR += cs[a] * fa + wgt<AT>(a) * (AT(EX[a]) * vsx[a] + AT(EY[a]) * vsy[a]);
-            tot += fa;
+        for (int a = 1; a < 9; a++) {
+            const bool outside = pull_outside(nb, a), bounced = (m & (1u << (OPP[a] - 1))) != 0;
+            AT c, vx, vy;
+            colour(a, c, vx, vy);
+            // from a solid node: the node's own colour state, reversed; across the inlet: pure
+            // red; across the outlet: the node's red fraction
+            c = outside ? (EX[a] > 0 ? AT(1) : cself) : (bounced ? cself : c);
+            vx = outside ? AT(0) : (bounced ? -vxs : vx);
+            vy = outside ? AT(0) : (bounced ? -vys : vy);
+            add_pull(a, wr[a < 5 ? 1 : 2] + d[a], c, vx, vy, rR, tot);
         }
         rB = tot - rR;
     }
@@ -406,65 +543,76 @@ __device__ __forceinline__ void wetting_correct(AT nsx, AT nsy, AT ct, AT st, AT
 }
 
 // MRT collision with Guo forcing (Eqs. 1, 2, 8 in moment space) of the deviations d (f = w rho0
-// + d), force F, local colour indicator rN; returns the post-collision deviations in o.
+// + d), force F, local colour indicator rN, colour densities rR and rB; returns the
+// post-collision deviations in o, the velocity of Eq. 17 and the new colour state (c, v) for the
+// interface normal n (Eq. 14).  Opposite populations are summed and subtracted first and the
+// moments built from those (24 operations), rho u is kept as the momentum rather than rebuilt
+// from u, and one reciprocal of the density serves the velocity and the red fraction.
 template <class AT>
-__device__ __forceinline__ void collide(DomC &D, const AT d[9], AT Fx, AT Fy, AT rN,
-                                        AT o[9], AT &rho_out, AT &ux_out, AT &uy_out) {
-    ParC<AT> &P = par(D, AT());
-    const AT rho0 = P.rho0;
-    const AT drho = d[0] + d[1] + d[2] + d[3] + d[4] + d[5] + d[6] + d[7] + d[8];
-    const AT sa = d[1] + d[2] + d[3] + d[4];
-    const AT sd = d[5] + d[6] + d[7] + d[8];
-    const AT jx = d[1] - d[3] + d[5] - d[6] - d[7] + d[8];
-    const AT jy = d[2] - d[4] + d[5] + d[6] - d[7] - d[8];
-    const AT m1 = AT(-4) * d[0] - sa + AT(2) * sd;
-    const AT m2 = AT(4) * d[0] - AT(2) * sa + sd;
-    const AT m4 = AT(-2) * (d[1] - d[3]) + (d[5] - d[6] - d[7] + d[8]);
-    const AT m6 = AT(-2) * (d[2] - d[4]) + (d[5] + d[6] - d[7] - d[8]);
-    const AT m7 = d[1] - d[2] + d[3] - d[4];
-    const AT m8 = d[5] - d[6] + d[7] - d[8];
+__device__ __forceinline__ void collide(ParC<AT> &P, const AT d[9], AT Fx, AT Fy, AT rN, AT rR, AT rB,
+                                        AT nx, AT ny, AT o[9], AT &ux, AT &uy, AT &c, AT &bx, AT &by) {
+#pragma clang fp contract(on)
+    const AT dx = d[1] - d[3], dy = d[2] - d[4], e1 = d[5] - d[7], e2 = d[6] - d[8];
+    const AT s1 = d[1] + d[3], s2 = d[2] + d[4], t1 = d[5] + d[7], t2 = d[6] + d[8];
+    const AT ex = e1 - e2, ey = e1 + e2;
+    const AT sa = s1 + s2, sd = t1 + t2;
+    const AT drho = d[0] + sa + sd;
+    const AT jx = dx + ex, jy = dy + ey;
+    const AT sd2 = AT(2) * sd - sa, sa2 = sd - AT(2) * sa;
+    const AT m1 = sd2 - AT(4) * d[0], m2 = AT(4) * d[0] + sa2;
+    const AT m4 = ex - AT(2) * dx, m6 = ey - AT(2) * dy;
+    const AT m7 = s1 - s2, m8 = t1 - t2;
 
-    const AT rho = rho0 + drho;
-    const AT inv_rho = rcp(rho);
-    const AT ux = (jx + AT(0.5) * Fx) * inv_rho;
-    const AT uy = (jy + AT(0.5) * Fy) * inv_rho;
+    const AT rs = rR + rB;
+    const AT ir = rcp(rs);
+    const AT px = AT(0.5) * Fx + jx, py = AT(0.5) * Fy + jy;  // rho u
+    ux = px * ir;
+    uy = py * ir;
     // Eqs. 18 and 5: 1/nu interpolated in rho^N, tau = 3 nu + 1/2, s_nu = 1/tau
-    const AT inv_nu = (AT(1) + rN) * P.inv2nu_r + (AT(1) - rN) * P.inv2nu_b;
-    const AT sv = inv_nu * rcp(AT(3) + AT(0.5) * inv_nu);
-    const AT se = P.s_e, seps = P.s_eps, sq = P.s_q;
-
-    const AT uu = ux * ux + uy * uy;
-    const AT r3uu = AT(3) * rho * uu;
-    const AT uF = ux * Fx + uy * Fy;
-    const AT p0 = drho;
-    const AT p1 = m1 - se * (m1 + AT(2) * drho - r3uu) + P.ke * uF;
-    const AT p2 = m2 - seps * (m2 - drho + r3uu) - P.keps * uF;
-    const AT p3 = rho * ux + AT(0.5) * Fx;
-    const AT p4 = m4 - sq * (m4 + rho * ux) - P.kq * Fx;
-    const AT p5 = rho * uy + AT(0.5) * Fy;
-    const AT p6 = m6 - sq * (m6 + rho * uy) - P.kq * Fy;
-    const AT p7 = m7 - sv * (m7 - rho * (ux * ux - uy * uy)) +
-                  (AT(1) - AT(0.5) * sv) * (AT(2) * (ux * Fx - uy * Fy));
-    const AT p8 = m8 - sv * (m8 - rho * ux * uy) + (AT(1) - AT(0.5) * sv) * (ux * Fy + uy * Fx);
+    const AT inv_nu = rN * P.inv_nu_diff + P.inv_nu_sum;
+    const AT sv = inv_nu * rcp(AT(0.5) * inv_nu + AT(3));
+    const AT qx = px * ux, qy = py * uy;
+    const AT r3 = AT(3) * (qx + qy), exx = qx - qy, exy = px * uy;
+    const AT fx = ux * Fx, fy = uy * Fy;
+    const AT uF = fx + fy, gxx = AT(2) * (fx - fy), fxy = ux * Fy;
+    const AT gxy = uy * Fx + fxy;
+    const AT h1 = AT(2) * drho + m1 - r3, h2 = m2 - drho + r3;
+    const AT p1 = P.ke * uF + m1, p2 = m2 - P.keps * uF;
+    const AT p3 = AT(0.5) * Fx + px, p5 = AT(0.5) * Fy + py;
+    const AT p4 = m4 - P.kq * Fx, p6 = m6 - P.kq * Fy;
+    const AT hv = AT(1) - AT(0.5) * sv;
+    const AT p7 = hv * gxx + m7, p8 = hv * gxy + m8;
+    const AT r1 = p1 - P.s_e * h1, r2 = p2 - P.s_eps * h2;
+    const AT r4 = p4 - P.s_q * (m4 + px), r6 = p6 - P.s_q * (m6 + py);
+    const AT r7 = p7 - sv * (m7 - exx), r8 = p8 - sv * (m8 - exy);
     // M^-1 = M^T diag(1/9, 1/36, 1/36, 1/6, 1/12, 1/6, 1/12, 1/4, 1/4)
-    const AT a0 = p0 * AT(1.0 / 9.0), a1 = p1 * AT(1.0 / 36.0), a2 = p2 * AT(1.0 / 36.0);
-    const AT a3 = p3 * AT(1.0 / 6.0), a4 = p4 * AT(1.0 / 12.0);
-    const AT a5 = p5 * AT(1.0 / 6.0), a6 = p6 * AT(1.0 / 12.0);
-    const AT a7 = p7 * AT(0.25), a8 = p8 * AT(0.25);
-    o[0] = a0 - AT(4) * a1 + AT(4) * a2;
-    const AT ax = a0 - a1 - AT(2) * a2;
-    o[1] = ax + a3 - AT(2) * a4 + a7;
-    o[2] = ax + a5 - AT(2) * a6 - a7;
-    o[3] = ax - a3 + AT(2) * a4 + a7;
-    o[4] = ax - a5 + AT(2) * a6 - a7;
-    const AT ad = a0 + AT(2) * a1 + a2;
-    o[5] = ad + a3 + a4 + a5 + a6 + a8;
-    o[6] = ad - a3 - a4 + a5 + a6 - a8;
-    o[7] = ad - a3 - a4 - a5 - a6 + a8;
-    o[8] = ad + a3 + a4 - a5 - a6 - a8;
-    rho_out = rho;
-    ux_out = ux;
-    uy_out = uy;
+    const AT a0 = drho * AT(1.0 / 9.0), a1 = r1 * AT(1.0 / 36.0), a2 = r2 * AT(1.0 / 36.0);
+    const AT a3 = p3 * AT(1.0 / 6.0), a4 = r4 * AT(1.0 / 12.0);
+    const AT a5 = p5 * AT(1.0 / 6.0), a6 = r6 * AT(1.0 / 12.0);
+    const AT a7 = r7 * AT(0.25), a8 = r8 * AT(0.25);
+    o[0] = AT(4) * (a2 - a1) + a0;
+    const AT bb = a0 - a1;
+    const AT ax = bb - AT(2) * a2;
+    const AT c1 = a3 - AT(2) * a4, c2 = a5 - AT(2) * a6;
+    const AT xx = ax + a7, yy = ax - a7;
+    o[1] = xx + c1;
+    o[3] = xx - c1;
+    o[2] = yy + c2;
+    o[4] = yy - c2;
+    const AT bd = a0 + a2;
+    const AT ad = AT(2) * a1 + bd;
+    const AT k1 = a3 + a4, k2 = a5 + a6;
+    const AT kp = k1 + k2, km = k1 - k2;
+    const AT dp = ad + a8, dm = ad - a8;
+    o[5] = dp + kp;
+    o[7] = dp - kp;
+    o[8] = dm + km;
+    o[6] = dm - km;
+    // recolouring state (Eq. 14)
+    c = quotient(rR, rs, ir);
+    const AT b = P.beta * rB * c;
+    bx = b * nx;
+    by = b * ny;
 }
 
 // Work item of block b: blocks are dealt round-robin to the 8 XCDs, so give each XCD a
@@ -563,8 +711,14 @@ struct Buf<uint16_t> {
 // of a row runs on the thread that gathered the row one iteration earlier.  LDS rings hold 2R
 // rows.  WV: some domain of the launch uses a wetting variant (Sec. III A); without it the
 // variant branches are compiled out.
+//
+// Wavefronts per SIMD (launch bounds): with FP32 arithmetic the kernel is held to 96 vector
+// registers, 5 wavefronts, with 4 to 7 of them in scratch; at 101 to 104 and 4 wavefronts, without
+// scratch, a step takes 64.4 against 69.2 us on 44 channels of 630 x 60 in binary16, 68 against 72
+// on twelve 400 x 400 cylinder boxes in c16, 326 against 335 on 60 channels of the sweep; FP32 on
+// 16384 x 512 alone prefers 4 (246 against 250).  With FP64 arithmetic it needs 159, 3 wavefronts.
 template <class T, int R, int C, bool WV>
-__global__ __launch_bounds__(TILE_LANES *R *C, sizeof(typename Codec<T>::AT) == 4 ? 4 : 2) void step_kernel(const StepArgs<T, typename Codec<T>::AT> A) {
+__global__ __launch_bounds__(TILE_LANES *R *C, sizeof(typename Codec<T>::AT) == 4 ? 5 : 3) void step_kernel(const StepArgs<T, typename Codec<T>::AT> A) {
     using AT = typename Codec<T>::AT;
     constexpr int Q = 2 * R;
     constexpr int TL = TILE_LANES * C;  // columns of the window: C wavefronts side by side
@@ -577,7 +731,7 @@ __global__ __launch_bounds__(TILE_LANES *R *C, sizeof(typename Codec<T>::AT) == 
     constexpr int GO = HX == HALO_X32 ? 1 : 0;
     __shared__ AT s_rn[Q][TL];
     __shared__ AT s_nx[Q][TL], s_ny[Q][TL];
-    __shared__ AT s_gx[Q][TL], s_gy[Q][TL];
+    __shared__ AT s_g[Q][TL];
     __shared__ AT s_c[Q][TL + 2 * GO], s_vx[Q][TL + 2 * GO], s_vy[Q][TL + 2 * GO];
     __shared__ AT s_wx[Q][TL], s_wy[Q][TL];
     __shared__ uint16_t s_m[Q][TL];
@@ -860,15 +1014,9 @@ __global__ __launch_bounds__(TILE_LANES *R *C, sizeof(typename Codec<T>::AT) == 
                     if ((m & SOLID_BND) && surface_energy) {
                         s_rn[sl][lane] = P.cos_t;  // surface-energy rule
                     } else if (m & SOLID_BND) {
-                        AT num = AT(0), den = AT(0);
-    #pragma unroll
-                        for (int a = 1; a < 9; a++) {
-                            if (m & (1u << (a - 1))) continue;
-                            const AT wa = wgt<AT>(a);
-                            num += wa * s_rn[(yb + EY[a]) & (Q - 1)][lanes_of[EX[a] + 1]];
-                            den += wa;
-                        }
-                        s_rn[sl][lane] = num * rcp(den);
+                        s_rn[sl][lane] = fluid_mean<AT>(m, [&](int ex, int ey) {
+                            return s_rn[(yb + ey) & (Q - 1)][lane + ex];
+                        });
                     }
                 }
                 replicate(s_rn, sl);
@@ -881,19 +1029,12 @@ __global__ __launch_bounds__(TILE_LANES *R *C, sizeof(typename Codec<T>::AT) == 
             const int sl = yc & (Q - 1);
             if (lane >= HX - 2 && lane < TL - (HX - 2) && yc >= y0 - HALO + 3 && yc < y1 + HALO - 3) {
                 const uint32_t m = s_m[sl][lane];
-                AT gx = AT(0), gy = AT(0), nx = AT(0), ny = AT(0);
+                AT g = AT(0), nx = AT(0), ny = AT(0);
                 if (!(m & SELF_SOLID)) {
-                    {
-                        AT sx = AT(0), sy = AT(0);
-#pragma unroll
-                        for (int a = 1; a < 9; a++) {
-                            const AT v = s_rn[(yc + EY[a]) & (Q - 1)][lanes_of[EX[a] + 1]];
-                            if (EX[a]) sx = acc_nc(sx, wgt<AT>(a), v, EX[a]);
-                            if (EY[a]) sy = acc_nc(sy, wgt<AT>(a), v, EY[a]);
-                        }
-                        gx = AT(3) * sx;
-                        gy = AT(3) * sy;
-                    }
+                    AT gx, gy;
+                    const auto rn_at = [&](int ex, int ey) { return s_rn[(yc + ey) & (Q - 1)][lane + ex]; };
+                    if (m & FLUID_BND) wall_gradient(rn_at, gx, gy);
+                    else gradient(rn_at, gx, gy);
                     // contact-line list: each node is recorded by the tile that outputs it
                     if (rec_cl && (m & FLUID_BND) && out_lane && yc >= y0 && yc < y1 &&
                         fsqrt(gx * gx + gy * gy) > eps) {
@@ -902,11 +1043,9 @@ __global__ __launch_bounds__(TILE_LANES *R *C, sizeof(typename Codec<T>::AT) == 
                     }
                     if ((m & FLUID_BND) && !surface_energy)
                         wetting_correct(s_wx[sl][lane], s_wy[sl][lane], P.cos_t, P.sin_t, eps, gx, gy);
-                    const AT g = fsqrt(gx * gx + gy * gy);
-                    if (g > eps) unit_normal(gx, gy, g, nx, ny);
+                    unit_normal(gx, gy, eps, g, nx, ny);
                 }
-                s_gx[sl][lane] = gx;
-                s_gy[sl][lane] = gy;
+                s_g[sl][lane] = g;
                 s_nx[sl][lane] = nx;
                 s_ny[sl][lane] = ny;
             }
@@ -922,20 +1061,13 @@ __global__ __launch_bounds__(TILE_LANES *R *C, sizeof(typename Codec<T>::AT) == 
                 if (lane >= HX - 1 && lane < TL - (HX - 1) && yd >= y0 - 1 && yd < y1 + 1) {
                     const uint32_t m = s_m[sl][lane];
                     if (m & SOLID_BND) {
-                        AT numx = AT(0), numy = AT(0), den = AT(0);
-    #pragma unroll
-                        for (int a = 1; a < 9; a++) {
-                            if (m & (1u << (a - 1))) continue;
-                            const AT wa = wgt<AT>(a);
-                            const int s2 = (yd + EY[a]) & (Q - 1);
-                            const int l2 = lanes_of[EX[a] + 1];
-                            numx += wa * s_nx[s2][l2];
-                            numy += wa * s_ny[s2][l2];
-                            den += wa;
-                        }
-                        const AT iden = rcp(den);
-                        s_nx[sl][lane] = numx * iden;
-                        s_ny[sl][lane] = numy * iden;
+                        AT vx, vy;
+                        fluid_mean2(m, [&](int ex, int ey, AT &x, AT &y) {
+                            x = s_nx[(yd + ey) & (Q - 1)][lane + ex];
+                            y = s_ny[(yd + ey) & (Q - 1)][lane + ex];
+                        }, vx, vy);
+                        s_nx[sl][lane] = vx;
+                        s_ny[sl][lane] = vy;
                     }
                 }
                 replicate(s_nx, sl);
@@ -957,68 +1089,24 @@ __global__ __launch_bounds__(TILE_LANES *R *C, sizeof(typename Codec<T>::AT) == 
             uint32_t vf = NOWHERE, vc = NOWHERE;
             const uint32_t me = s_m[sl][lane];
             if (out_lane && ye >= y0 && ye < y1 && !(me & SELF_SOLID)) {
-                AT dxnx = AT(0), dynx = AT(0), dxny = AT(0), dyny = AT(0);
+                AT dxnx, dynx, dxny, dyny;
                 if (scheme_b && (me & FLUID_BND)) {
-                    // Eq. 48: weighted mean of the differences to the fluid neighbours
-                    const AT nx0 = s_nx[sl][lane], ny0 = s_ny[sl][lane];
-                    AT den = AT(0);
-#pragma unroll
-                    for (int a = 1; a < 9; a++) {
-                        if (me & (1u << (a - 1))) continue;
-                        const int s2 = (ye + EY[a]) & (Q - 1);
-                        const int l2 = lanes_of[EX[a] + 1];
-                        const AT vx = s_nx[s2][l2] - nx0, vy = s_ny[s2][l2] - ny0;
-                        if (EX[a]) {
-                            dxnx += wgt<AT>(a) * vx * AT(EX[a]);
-                            dxny += wgt<AT>(a) * vy * AT(EX[a]);
-                        }
-                        if (EY[a]) {
-                            dynx += wgt<AT>(a) * vx * AT(EY[a]);
-                            dyny += wgt<AT>(a) * vy * AT(EY[a]);
-                        }
-                        den += wgt<AT>(a);
-                    }
-                    const AT iden = rcp(den);
-                    dxnx *= iden;
-                    dynx *= iden;
-                    dxny *= iden;
-                    dyny *= iden;
+                    one_sided_gradient(me, [&](int ex, int ey, AT &x, AT &y) {
+                        x = s_nx[(ye + ey) & (Q - 1)][lane + ex];
+                        y = s_ny[(ye + ey) & (Q - 1)][lane + ex];
+                    }, dxnx, dynx, dxny, dyny);
                 } else {
-#pragma unroll
-                    for (int a = 1; a < 9; a++) {
-                        const int s2 = (ye + EY[a]) & (Q - 1);
-                        const int l2 = lanes_of[EX[a] + 1];
-                        const AT vx = s_nx[s2][l2], vy = s_ny[s2][l2];
-                        if (EX[a]) {
-                            dxnx += wgt<AT>(a) * vx * AT(EX[a]);
-                            dxny += wgt<AT>(a) * vy * AT(EX[a]);
-                        }
-                        if (EY[a]) {
-                            dynx += wgt<AT>(a) * vx * AT(EY[a]);
-                            dyny += wgt<AT>(a) * vy * AT(EY[a]);
-                        }
-                    }
-                    dxnx *= AT(3);
-                    dynx *= AT(3);
-                    dxny *= AT(3);
-                    dyny *= AT(3);
+                    gradient([&](int ex, int ey) { return s_nx[(ye + ey) & (Q - 1)][lane + ex]; }, dxnx, dynx);
+                    gradient([&](int ex, int ey) { return s_ny[(ye + ey) & (Q - 1)][lane + ex]; }, dxny, dyny);
                 }
                 const AT nx = s_nx[sl][lane], ny = s_ny[sl][lane];
-                const AT gx = s_gx[sl][lane], gy = s_gy[sl][lane];
-                const AT kappa = -nx * nx * dyny - ny * ny * dxnx + nx * ny * (dynx + dxny);
-                const AT Fx = P.half_sigma * kappa * gx;
-                const AT Fy = P.half_sigma * kappa * gy;
-                AT rho;
-                collide(D, d, Fx, Fy, rN, o, rho, ux, uy);
-                const AT rs = rR + rB;
-                c = quotient(rR, rs);
-                const AT b = P.beta * rB * c;
-                bx = b * nx;
-                by = b * ny;
+                AT Fx, Fy;
+                csf_force(P.half_sigma, s_g[sl][lane], nx, ny, dxnx, dynx, dxny, dyny, Fx, Fy);
+                collide(P, d, Fx, Fy, rN, rR, rB, nx, ny, o, ux, uy, c, bx, by);
                 const uint32_t nd = node_of(ye);
                 vf = nd * SB;
                 vc = nd * CB;
-                if (!isfinite(rho + ux + uy)) atomicOr(A.flag, 1);  // any NaN or overflow
+                if (!isfinite(rR + rB + ux + uy)) atomicOr(A.flag, 1);  // any NaN or overflow
             }
             if (A.diag) {
                 c = ux;
@@ -1169,7 +1257,7 @@ __global__ __launch_bounds__(TILE_LANES *R, 2) void pair_kernel(const StepArgs<T
     constexpr uint32_t SB = sizeof(T), CB = sizeof(AT);
     __shared__ AT s_rn[Q][TW];
     __shared__ AT s_nx[Q][TW], s_ny[Q][TW];
-    __shared__ AT s_gx[Q][TW], s_gy[Q][TW];
+    __shared__ AT s_g[Q][TW];
     __shared__ AT s_c[Q][TW], s_vx[Q][TW], s_vy[Q][TW];
     __shared__ AT s_wx[Q][TW], s_wy[Q][TW];
     __shared__ uint16_t s_m[Q][TW];
@@ -1430,15 +1518,9 @@ __global__ __launch_bounds__(TILE_LANES *R, 2) void pair_kernel(const StepArgs<T
                         if ((m & SOLID_BND) && surface_energy) {
                             s_rn[sl][ck] = P.cos_t;
                         } else if (m & SOLID_BND) {
-                            AT num = AT(0), den = AT(0);
-#pragma unroll
-                            for (int a = 1; a < 9; a++) {
-                                if (m & (1u << (a - 1))) continue;
-                                const AT wa = wgt<AT>(a);
-                                num += wa * s_rn[(yb + EY[a]) & (Q - 1)][ck + EX[a]];
-                                den += wa;
-                            }
-                            s_rn[sl][ck] = num * rcp(den);
+                            s_rn[sl][ck] = fluid_mean<AT>(m, [&](int ex, int ey) {
+                                return s_rn[(yb + ey) & (Q - 1)][ck + ex];
+                            });
                         }
                     }
                 }
@@ -1456,17 +1538,12 @@ __global__ __launch_bounds__(TILE_LANES *R, 2) void pair_kernel(const StepArgs<T
                     const int ck = col[k];
                     if (ck >= 3 && ck < TW - 3) {
                         const uint32_t m = s_m[sl][ck];
-                        AT gx = AT(0), gy = AT(0), nx = AT(0), ny = AT(0);
+                        AT g = AT(0), nx = AT(0), ny = AT(0);
                         if (!(m & SELF_SOLID)) {
-                            AT sx = AT(0), sy = AT(0);
-#pragma unroll
-                            for (int a = 1; a < 9; a++) {
-                                const AT v = s_rn[(yc + EY[a]) & (Q - 1)][ck + EX[a]];
-                                if (EX[a]) sx = acc_nc(sx, wgt<AT>(a), v, EX[a]);
-                                if (EY[a]) sy = acc_nc(sy, wgt<AT>(a), v, EY[a]);
-                            }
-                            gx = AT(3) * sx;
-                            gy = AT(3) * sy;
+                            AT gx, gy;
+                            const auto rn_at = [&](int ex, int ey) { return s_rn[(yc + ey) & (Q - 1)][ck + ex]; };
+                            if (m & FLUID_BND) wall_gradient(rn_at, gx, gy);
+                            else gradient(rn_at, gx, gy);
                             if (rec_cl && (m & FLUID_BND) && out[k] && yc >= y0 && yc < y1 &&
                                 fsqrt(gx * gx + gy * gy) > eps) {
                                 const int q = atomicAdd(A.cl_count, 1);
@@ -1474,11 +1551,9 @@ __global__ __launch_bounds__(TILE_LANES *R, 2) void pair_kernel(const StepArgs<T
                             }
                             if ((m & FLUID_BND) && !surface_energy)
                                 wetting_correct(s_wx[sl][ck], s_wy[sl][ck], P.cos_t, P.sin_t, eps, gx, gy);
-                            const AT g = fsqrt(gx * gx + gy * gy);
-                            if (g > eps) unit_normal(gx, gy, g, nx, ny);
+                            unit_normal(gx, gy, eps, g, nx, ny);
                         }
-                        s_gx[sl][ck] = gx;
-                        s_gy[sl][ck] = gy;
+                        s_g[sl][ck] = g;
                         s_nx[sl][ck] = nx;
                         s_ny[sl][ck] = ny;
                     }
@@ -1499,19 +1574,13 @@ __global__ __launch_bounds__(TILE_LANES *R, 2) void pair_kernel(const StepArgs<T
                     if (ck >= 4 && ck < TW - 4) {
                         const uint32_t m = s_m[sl][ck];
                         if (m & SOLID_BND) {
-                            AT numx = AT(0), numy = AT(0), den = AT(0);
-#pragma unroll
-                            for (int a = 1; a < 9; a++) {
-                                if (m & (1u << (a - 1))) continue;
-                                const AT wa = wgt<AT>(a);
-                                const int s2 = (yd + EY[a]) & (Q - 1);
-                                numx += wa * s_nx[s2][ck + EX[a]];
-                                numy += wa * s_ny[s2][ck + EX[a]];
-                                den += wa;
-                            }
-                            const AT iden = rcp(den);
-                            s_nx[sl][ck] = numx * iden;
-                            s_ny[sl][ck] = numy * iden;
+                            AT vx, vy;
+                            fluid_mean2(m, [&](int ex, int ey, AT &x, AT &y) {
+                                x = s_nx[(yd + ey) & (Q - 1)][ck + ex];
+                                y = s_ny[(yd + ey) & (Q - 1)][ck + ex];
+                            }, vx, vy);
+                            s_nx[sl][ck] = vx;
+                            s_ny[sl][ck] = vy;
                         }
                     }
                 }
@@ -1537,62 +1606,21 @@ __global__ __launch_bounds__(TILE_LANES *R, 2) void pair_kernel(const StepArgs<T
                 for (int a = 0; a < 9; a++) o[k][a] = AT(0);
                 const uint32_t me = s_m[sl][ck];
                 if (out[k] && row_out && !(me & SELF_SOLID)) {
-                    AT dxnx = AT(0), dynx = AT(0), dxny = AT(0), dyny = AT(0);
+                    AT dxnx, dynx, dxny, dyny;
                     if (scheme_b && (me & FLUID_BND)) {
-                        const AT nx0 = s_nx[sl][ck], ny0 = s_ny[sl][ck];
-                        AT den = AT(0);
-#pragma unroll
-                        for (int a = 1; a < 9; a++) {
-                            if (me & (1u << (a - 1))) continue;
-                            const int s2 = (ye + EY[a]) & (Q - 1);
-                            const AT vx = s_nx[s2][ck + EX[a]] - nx0, vy = s_ny[s2][ck + EX[a]] - ny0;
-                            if (EX[a]) {
-                                dxnx += wgt<AT>(a) * vx * AT(EX[a]);
-                                dxny += wgt<AT>(a) * vy * AT(EX[a]);
-                            }
-                            if (EY[a]) {
-                                dynx += wgt<AT>(a) * vx * AT(EY[a]);
-                                dyny += wgt<AT>(a) * vy * AT(EY[a]);
-                            }
-                            den += wgt<AT>(a);
-                        }
-                        const AT iden = rcp(den);
-                        dxnx *= iden;
-                        dynx *= iden;
-                        dxny *= iden;
-                        dyny *= iden;
+                        one_sided_gradient(me, [&](int ex, int ey, AT &x, AT &y) {
+                            x = s_nx[(ye + ey) & (Q - 1)][ck + ex];
+                            y = s_ny[(ye + ey) & (Q - 1)][ck + ex];
+                        }, dxnx, dynx, dxny, dyny);
                     } else {
-#pragma unroll
-                        for (int a = 1; a < 9; a++) {
-                            const int s2 = (ye + EY[a]) & (Q - 1);
-                            const AT vx = s_nx[s2][ck + EX[a]], vy = s_ny[s2][ck + EX[a]];
-                            if (EX[a]) {
-                                dxnx += wgt<AT>(a) * vx * AT(EX[a]);
-                                dxny += wgt<AT>(a) * vy * AT(EX[a]);
-                            }
-                            if (EY[a]) {
-                                dynx += wgt<AT>(a) * vx * AT(EY[a]);
-                                dyny += wgt<AT>(a) * vy * AT(EY[a]);
-                            }
-                        }
-                        dxnx *= AT(3);
-                        dynx *= AT(3);
-                        dxny *= AT(3);
-                        dyny *= AT(3);
+                        gradient([&](int ex, int ey) { return s_nx[(ye + ey) & (Q - 1)][ck + ex]; }, dxnx, dynx);
+                        gradient([&](int ex, int ey) { return s_ny[(ye + ey) & (Q - 1)][ck + ex]; }, dxny, dyny);
                     }
                     const AT nx = s_nx[sl][ck], ny = s_ny[sl][ck];
-                    const AT gx = s_gx[sl][ck], gy = s_gy[sl][ck];
-                    const AT kappa = -nx * nx * dyny - ny * ny * dxnx + nx * ny * (dynx + dxny);
-                    const AT Fx = P.half_sigma * kappa * gx;
-                    const AT Fy = P.half_sigma * kappa * gy;
-                    AT rho;
-                    collide(D, d[k], Fx, Fy, rN[k], o[k], rho, ux, uy);
-                    const AT rs = rR[k] + rB[k];
-                    c = quotient(rR[k], rs);
-                    const AT b = P.beta * rB[k] * c;
-                    bx = b * nx;
-                    by = b * ny;
-                    if (!isfinite(rho + ux + uy)) atomicOr(A.flag, 1);
+                    AT Fx, Fy;
+                    csf_force(P.half_sigma, s_g[sl][ck], nx, ny, dxnx, dynx, dxny, dyny, Fx, Fy);
+                    collide(P, d[k], Fx, Fy, rN[k], rR[k], rB[k], nx, ny, o[k], ux, uy, c, bx, by);
+                    if (!isfinite(rR[k] + rB[k] + ux + uy)) atomicOr(A.flag, 1);
                 }
                 if (A.diag) {
                     c = ux;
