@@ -198,6 +198,9 @@ int64_t lbm_steps_taken(const lbm_ctx *ctx);
  *   cols 1, cols_per_lane 2: 128-column tiles with 116 output columns, each lane updating two
  *     adjacent nodes; only for the FP32-arithmetic storages and batches whose domains all have an
  *     even nx (never the built-in choice; lbm_autotune weighs it).
+ * Blocks of 8 with one column and lane width 1 hold an item of 8 rows, or of 24 rows with FP32
+ * arithmetic, as a whole instead of marching through it (56 output columns in every storage): the
+ * built-in choice for small and medium batches.
  * 0 selects the built-in value.  Rebuilds the schedule.  Every shape computes the same method
  * with the same per-node arithmetic (FP64: the same bits; FP32 arithmetic: each shape is checked
  * against the FP64 oracle to the storage's rounding).  Synchronises the stream.  LBM_EINVAL for a

@@ -64,8 +64,8 @@ struct Layout {
            mass_out = 0, flag = 0, scratch_bytes = 0;
 };
 
-int strips_of(const lbm_domain_desc &d, int cols, int npl, int storage) {
-    return (d.nx + tile_out(cols, npl, storage) - 1) / tile_out(cols, npl, storage);
+int strips_of(const lbm_domain_desc &d, const TileShape &t, int storage) {
+    return (d.nx + t.out(storage) - 1) / t.out(storage);
 }
 
 Layout make_layout(const lbm_domain_desc *d, int n, int storage) {
@@ -74,7 +74,7 @@ Layout make_layout(const lbm_domain_desc *d, int n, int storage) {
     for (int i = 0; i < n; i++) {
         nodes += align_up((size_t)d[i].nx * d[i].ny, 64);
         rows += d[i].ny;
-        cap += (size_t)strips_of(d[i], 1, 1, 0) * ((d[i].ny + 7) / 8);  // the narrowest strips
+        cap += (size_t)strips_of(d[i], {64, 4, 1, 1}, 0) * ((d[i].ny + 7) / 8);  // the narrowest strips
     }
     L.plane = align_up(std::max<size_t>(nodes, 64), 128);
     L.rows = rows;
@@ -252,10 +252,9 @@ struct lbm_ctx {
     std::vector<lbm_domain_desc> desc;   // host pointers are not kept valid: sizes only
     std::vector<DomDev> doms;
     std::vector<WorkItem> items;
-    int chunk_rows = 0;
-    int waves = 0;    // wavefronts (tile rows advanced per iteration) of the step kernel
-    int cols = 1;     // wavefronts side by side in a tile row (tile width 64 cols)
-    int npl = 1;      // node columns per lane: 1, or 2 (pair kernel; tile width 128, cols = 1)
+    // rows per work item, wavefronts (tile rows advanced per iteration), wavefronts side by side
+    // in a tile row, and node columns per lane (2: pair kernel) of the step
+    TileShape tile{0, 0, 1, 1};
     bool variants = false;  // some domain uses a wetting variant (LBM_WET_*)
     int parity = 0;   // buffer holding the current state
     int own = 1;      // current state is a node-local snapshot
@@ -388,18 +387,18 @@ AnyArgs make_diag_args(const lbm_ctx *c, int cl_dom = -1) {
 // stream a narrow band of every plane, which measured markedly faster than a strip at a time.
 // A domain with more items than one run is cut into strip groups of about one run each, so
 // that every XCD works through a compact region and neighbouring strips share its L2.
-std::vector<WorkItem> build_items(const std::vector<lbm_domain_desc> &d, int chunk, int cols, int npl,
-                                  int storage) {
+std::vector<WorkItem> build_items(const std::vector<lbm_domain_desc> &d, const TileShape &t, int storage) {
+    const int chunk = t.chunk;
     size_t total = 0;
     for (const auto &q : d) {
         const int nch = std::max(1, (q.ny + chunk - 1) / chunk);
-        total += (size_t)strips_of(q, cols, npl, storage) * nch;
+        total += (size_t)strips_of(q, t, storage) * nch;
     }
     const size_t run = std::max<size_t>(1, total / 8);
     std::vector<WorkItem> out;
     out.reserve(total);
     for (int i = 0; i < (int)d.size(); i++) {
-        const int ny = d[i].ny, S = strips_of(d[i], cols, npl, storage);
+        const int ny = d[i].ny, S = strips_of(d[i], t, storage);
         const int nch = std::max(1, (ny + chunk - 1) / chunk);
         const int ch = ((ny + nch - 1) / nch + 3) / 4 * 4;
         const size_t items = (size_t)S * nch;
@@ -409,7 +408,7 @@ std::vector<WorkItem> build_items(const std::vector<lbm_domain_desc> &d, int chu
             for (int k = 0; k < nch; k++) {
                 const int y0 = k * ch, y1 = std::min(ny, y0 + ch);
                 if (y0 >= y1) continue;
-                for (int s = s0; s < s1; s++) out.push_back(WorkItem{i, s * tile_out(cols, npl, storage), y0, y1});
+                for (int s = s0; s < s1; s++) out.push_back(WorkItem{i, s * t.out(storage), y0, y1});
             }
         }
     }
@@ -423,21 +422,44 @@ std::vector<WorkItem> build_items(const std::vector<lbm_domain_desc> &d, int chu
 // (15 or 44 of 630 x 60) ran 15-23 % faster in 16-row chunks than in 8-row ones, whose halo
 // rows double the work, while a single 2000 x 100 channel (266 items at 16 rows) ran fastest
 // in 8-row chunks, where more items outweigh the halo.
-int auto_chunk(const std::vector<lbm_domain_desc> &d, int cols, int npl, int storage) {
+int auto_chunk(const std::vector<lbm_domain_desc> &d, TileShape t, int storage) {
+    const auto items = [&](int ch) {
+        t.chunk = ch;
+        return build_items(d, t, storage).size();
+    };
     for (int ch : {64, 48, 32, 24})
-        if (build_items(d, ch, cols, npl, storage).size() >= 4096) return ch;
+        if (items(ch) >= 4096) return ch;
     for (int ch : {16, 12})
-        if (build_items(d, ch, cols, npl, storage).size() >= 512) return ch;
+        if (items(ch) >= 512) return ch;
     return 8;
 }
 
 // Blocks of 4 tile rows (one wavefront per SIMD) measured at least as fast as blocks of 8 for
 // every storage type.
-int default_waves(int) { return 4; }
+constexpr int DEFAULT_WAVES = 4;
 // One-wavefront tiles.  Tiles two wavefronts wide (120 output columns of 128; 118 with FP64
 // arithmetic) repeat fewer halo columns but measured 3-5 % slower on the sweep (8-wavefront
 // barriers, 2 blocks per CU).
-int default_cols(int) { return 1; }
+constexpr int DEFAULT_COLS = 1;
+// The built-in shape of a batch: the patch kernel, which takes a work item at once, while its
+// repeated halo rows cost less than the march's iterations (us per step on an MI355X, patch
+// against the best march):
+//  FP32 arithmetic, binary16 / FP32 storage: items of 8 rows up to 1536 of them (234 items 8.3
+//    against 20, 1404 items 20.4 against 33; 1600 items 24 where items of 24 rows take 20), then
+//    items of 24 rows: 44 channels 630 x 60 44 / 45 against 64, 16384 x 512 183 / 226 against
+//    190 / 250.  In the 16-bit storages only up to 8192 items (60 channels of the sweep, 12240
+//    items: 335 against 327 in 64-row marches); an FP32 step is bound by HBM there and gains.
+//  FP64: items of 8 rows up to 10240 (234 items 10.6 against 21.7, 4224 items 113 against 119,
+//    9669 items 242 against 248; 19338 items 441 against 411).
+constexpr size_t PATCH_ITEMS = 1536, PATCH_TALL_ITEMS_16 = 8192, PATCH_ITEMS_F64 = 10240;
+TileShape builtin_tile(const std::vector<lbm_domain_desc> &d, int storage) {
+    const TileShape patch{PATCH_ROWS, 8, 1, 1}, tall{PATCH_TALL_ROWS, 8, 1, 1};
+    if (build_items(d, patch, storage).size() <= (storage == 0 ? PATCH_ITEMS_F64 : PATCH_ITEMS)) return patch;
+    if (storage == 1 || (storage > 1 && build_items(d, tall, storage).size() <= PATCH_TALL_ITEMS_16)) return tall;
+    TileShape t{0, DEFAULT_WAVES, DEFAULT_COLS, 1};
+    t.chunk = auto_chunk(d, t, storage);
+    return t;
+}
 // The pair kernel (two node columns per lane) needs FP32 arithmetic and an even width in every
 // domain.  It is offered to lbm_set_tile and the autotuner but is not the built-in choice: at the
 // two wavefronts per SIMD its register use allows, it measured slower than the one-column kernel
@@ -448,7 +470,6 @@ bool pair_allowed(int storage, const std::vector<lbm_domain_desc> &d) {
         if (q.nx % 2) return false;
     return true;
 }
-int default_npl(int, const std::vector<lbm_domain_desc> &) { return 1; }
 
 int upload_items(lbm_ctx *c) {
     if (c->items.size() > c->L.items_cap) return fail(LBM_EINVAL, "work-item table overflow");
@@ -461,8 +482,7 @@ int upload_items(lbm_ctx *c) {
 // One step launched directly on stream s, with the context's current arguments.
 hipError_t step_once(lbm_ctx *c, hipStream_t s) {
     AnyArgs a = make_args(c, c->parity);
-    const hipError_t e = launch_step(c->storage, a.bytes, (int)c->items.size(), c->waves, c->cols, c->npl,
-                                     c->variants, s);
+    const hipError_t e = launch_step(c->storage, a.bytes, (int)c->items.size(), c->tile, c->variants, s);
     if (e != hipSuccess) return e;
     c->parity ^= 1;
     c->own = 0;
@@ -650,11 +670,8 @@ int lbm_create(const lbm_domain_desc *domains, int n, int storage, void *state_d
     c->L = L;
     c->desc.assign(domains, domains + n);
     c->doms.resize(n);
-    c->waves = default_waves(storage);
-    c->npl = default_npl(storage, c->desc);
-    c->cols = default_cols(storage);
-    c->chunk_rows = auto_chunk(c->desc, c->cols, c->npl, c->storage);
-    c->items = build_items(c->desc, c->chunk_rows, c->cols, c->npl, c->storage);
+    c->tile = builtin_tile(c->desc, storage);
+    c->items = build_items(c->desc, c->tile, storage);
     if (hipHostMalloc((void **)&c->mass_host, (2 * (size_t)n + 2) * sizeof(double)) != hipSuccess ||
         hipHostMalloc((void **)&c->flag_host, 64) != hipSuccess) {
         delete c;
@@ -740,7 +757,7 @@ int lbm_autotune(lbm_ctx *c, int steps, void *save_dev, double *out_host) {
     HIP_OK(hipStreamSynchronize(c->stream));
     const int flag0 = *c->flag_host;
     struct Trial {
-        int chunk, waves, cols, npl;
+        TileShape tile;
         double ms;
     };
     std::vector<Trial> trials;
@@ -751,14 +768,15 @@ int lbm_autotune(lbm_ctx *c, int steps, void *save_dev, double *out_host) {
         if (sh[2] == 2 && !pairs) continue;
         std::vector<WorkItem> prev;
         for (int ch : {8, 12, 16, 24, 32, 48, 64}) {
-            std::vector<WorkItem> it = build_items(c->desc, ch, sh[1], sh[2], c->storage);
+            const TileShape t{ch, sh[0], sh[1], sh[2]};
+            std::vector<WorkItem> it = build_items(c->desc, t, c->storage);
             // a taller chunk that cuts no domain differently is the same schedule
             if (it.size() == prev.size() &&
                 std::equal(it.begin(), it.end(), prev.begin(), [](const WorkItem &a, const WorkItem &b) {
                     return a.dom == b.dom && a.x0 == b.x0 && a.y0 == b.y0 && a.y1 == b.y1;
                 }))
                 continue;
-            trials.push_back({ch, sh[0], sh[1], sh[2], 0.0});
+            trials.push_back({t, 0.0});
             prev.swap(it);
         }
     }
@@ -770,11 +788,8 @@ int lbm_autotune(lbm_ctx *c, int steps, void *save_dev, double *out_host) {
     }
     // one untimed step, then `steps` timed steps on the stream, per shape
     auto time_shape = [&](const Trial &t, double &ms) -> hipError_t {
-        c->chunk_rows = t.chunk;
-        c->waves = t.waves;
-        c->cols = t.cols;
-        c->npl = t.npl;
-        c->items = build_items(c->desc, t.chunk, t.cols, t.npl, c->storage);
+        c->tile = t.tile;
+        c->items = build_items(c->desc, t.tile, c->storage);
         if (upload_items(c)) return hipErrorInvalidValue;
         hipError_t e = step_once(c, c->stream);
         if (e == hipSuccess) e = hipEventRecord(e0, c->stream);
@@ -802,11 +817,8 @@ int lbm_autotune(lbm_ctx *c, int steps, void *save_dev, double *out_host) {
     (void)hipEventDestroy(e1);
     if (e != hipSuccess) return fail(LBM_EDEVICE, "autotune: %s", hipGetErrorString(e));
     const Trial best = trials[0];
-    c->chunk_rows = best.chunk;
-    c->waves = best.waves;
-    c->cols = best.cols;
-    c->npl = best.npl;
-    c->items = build_items(c->desc, best.chunk, best.cols, best.npl, c->storage);
+    c->tile = best.tile;
+    c->items = build_items(c->desc, best.tile, c->storage);
     rc = upload_items(c);
     if (rc) return rc;
     drop_graphs(c);
@@ -817,11 +829,11 @@ int lbm_autotune(lbm_ctx *c, int steps, void *save_dev, double *out_host) {
                           c->stream));
     HIP_OK(hipStreamSynchronize(c->stream));
     if (out_host) {
-        out_host[0] = best.chunk;
-        out_host[1] = best.waves;
-        out_host[2] = best.cols;
+        out_host[0] = best.tile.chunk;
+        out_host[1] = best.tile.waves;
+        out_host[2] = best.tile.cols;
         out_host[3] = best.ms / 2.0;  // mean of the two timings
-        out_host[4] = best.npl;
+        out_host[4] = best.tile.npl;
     }
     return LBM_OK;
 }
@@ -847,7 +859,7 @@ int lbm_read_fields(lbm_ctx *c, int domain, uint32_t which, double *out_dev, siz
     }
     if (which & 24u) {
         AnyArgs da = make_diag_args(c);
-        HIP_OK(launch_step(c->storage, da.bytes, (int)c->items.size(), c->waves, c->cols, c->npl, c->variants, c->stream));
+        HIP_OK(launch_step(c->storage, da.bytes, (int)c->items.size(), c->tile, c->variants, c->stream));
         double *ox = (which & 8u) ? out_dev + (p++) * nn : nullptr;
         double *oy = (which & 16u) ? out_dev + p * nn : nullptr;
         HIP_OK(launch_velocity_copy(c->storage, a.bytes, domain, c->diag + diag_layout(c).u, ox, oy,
@@ -882,31 +894,32 @@ int lbm_set_tile(lbm_ctx *c, int chunk_rows, int waves, int cols, int cols_per_l
     if (cols != 0 && cols != 1 && cols != 2) return fail(LBM_EINVAL, "cols must be 0, 1 or 2");
     if (cols_per_lane != 0 && cols_per_lane != 1 && cols_per_lane != 2)
         return fail(LBM_EINVAL, "cols_per_lane must be 0, 1 or 2");
-    const int w = waves ? waves : default_waves(c->storage);
-    int npl = cols_per_lane;
-    if (npl == 0) npl = cols == 2 ? 1 : default_npl(c->storage, c->desc);
-    const int k = cols ? cols : default_cols(c->storage);
+    const int w = waves ? waves : DEFAULT_WAVES;
+    const int npl = cols_per_lane ? cols_per_lane : 1;
+    const int k = cols ? cols : DEFAULT_COLS;
     if (w == 8 && k == 2) return fail(LBM_EINVAL, "tiles of 8 x 2 wavefronts are not provided");
     if (npl == 2 && k != 1) return fail(LBM_EINVAL, "two columns per lane need one wavefront per tile row");
     if (npl == 2 && !pair_allowed(c->storage, c->desc))
         return fail(LBM_EINVAL, "two columns per lane need FP32 arithmetic and an even nx in every domain");
     HIP_OK(hipStreamSynchronize(c->stream));
     drop_graphs(c);
-    c->waves = w;
-    c->cols = k;
-    c->npl = npl;
-    c->chunk_rows = chunk_rows ? chunk_rows : auto_chunk(c->desc, c->cols, c->npl, c->storage);
-    c->items = build_items(c->desc, c->chunk_rows, c->cols, c->npl, c->storage);
+    TileShape t{chunk_rows, w, k, npl};
+    if (!chunk_rows) {
+        if (!waves && k == 1 && npl == 1) t = builtin_tile(c->desc, c->storage);
+        else t.chunk = auto_chunk(c->desc, t, c->storage);
+    }
+    c->tile = t;
+    c->items = build_items(c->desc, t, c->storage);
     return upload_items(c);
 }
 
 int lbm_get_tile(const lbm_ctx *c, int *shape_out) {
     if (!c || !shape_out) return fail(LBM_EINVAL, "null argument");
-    shape_out[0] = c->chunk_rows;
-    shape_out[1] = c->waves;
-    shape_out[2] = c->cols;
+    shape_out[0] = c->tile.chunk;
+    shape_out[1] = c->tile.waves;
+    shape_out[2] = c->tile.cols;
     shape_out[3] = (int)c->items.size();
-    shape_out[4] = c->npl;
+    shape_out[4] = c->tile.npl;
     return LBM_OK;
 }
 
@@ -968,7 +981,7 @@ int lbm_diag_velocity(lbm_ctx *c, int snapshot, double *out_host) {
     if (!c->diag) return fail(LBM_ESTATE, "no diagnostics buffer attached (lbm_diag_attach)");
     const DiagLayout DL = diag_layout(c);
     AnyArgs da = make_diag_args(c);
-    HIP_OK(launch_step(c->storage, da.bytes, (int)c->items.size(), c->waves, c->cols, c->npl, c->variants, c->stream));
+    HIP_OK(launch_step(c->storage, da.bytes, (int)c->items.size(), c->tile, c->variants, c->stream));
     double *res = reinterpret_cast<double *>(c->diag + DL.res);
     HIP_OK(launch_velocity_stats(c->storage, da.bytes, c->n, c->diag + DL.u,
                                  c->snap_valid ? c->diag + DL.snap : nullptr,
@@ -1055,7 +1068,7 @@ int lbm_diag_contact_line(lbm_ctx *c, int domain, int32_t *out_host, int cap, in
     int *dcount = reinterpret_cast<int *>(c->diag + DL.cl_count);
     HIP_OK(hipMemsetAsync(dcount, 0, sizeof(int), c->stream));
     AnyArgs da = make_diag_args(c, domain);
-    HIP_OK(launch_step(c->storage, da.bytes, (int)c->items.size(), c->waves, c->cols, c->npl, c->variants, c->stream));
+    HIP_OK(launch_step(c->storage, da.bytes, (int)c->items.size(), c->tile, c->variants, c->stream));
     HIP_OK(hipMemcpyAsync(c->rows_host, dcount, sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIP_OK(hipStreamSynchronize(c->stream));
     const int n = c->rows_host[0];

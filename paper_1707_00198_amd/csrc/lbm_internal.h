@@ -26,9 +26,22 @@ inline int halo_x(int storage) { return storage == 0 ? HALO_X64 : HALO_X32; }
 // Output columns of a tile: `cols` wavefronts side by side with one column per lane, or one
 // wavefront with two columns per lane (npl = 2: 128 columns, halo 6).  The FP64 storage uses
 // the one-column kernel only.
-inline int tile_out(int cols, int npl, int storage) {
-    return npl == 2 ? 2 * TILE_LANES - 12 : TILE_LANES * cols - 2 * halo_x(storage);
-}
+//
+// Work items of 8 rows and, with FP32 arithmetic, of 24 rows on blocks of 8 run on the patch
+// kernel, which holds a whole item with its halo and takes the colour state around it from extra
+// LDS rows and columns in every storage.
+constexpr int PATCH_ROWS = 8, PATCH_TALL_ROWS = 24, PATCH_HALO = 4;
+struct TileShape {
+    int chunk, waves, cols, npl;
+    bool patch(bool f64) const {
+        return waves == 8 && cols == 1 && npl == 1 &&
+               (chunk == PATCH_ROWS || (chunk == PATCH_TALL_ROWS && !f64));
+    }
+    int out(int storage) const {
+        if (npl == 2) return 2 * TILE_LANES - 12;
+        return TILE_LANES * cols - 2 * (patch(storage == 0) ? PATCH_HALO : halo_x(storage));
+    }
+};
 
 // Per-domain parameters in one arithmetic type, with the constant factors of the collision
 // precomputed: ke = 6 (1 - s_e / 2), keps = 6 (1 - s_eps / 2), kq = 1 - s_q / 2 (the forcing
@@ -113,8 +126,8 @@ struct StepArgs {
 // npl: node columns per lane, 1, or 2 (the pair kernel: FP32-arithmetic storages, cols = 1,
 // every domain of even width; the tile is then 128 columns wide).
 // variants: some domain has nonzero wetting flags (selects the kernel that tests them).
-hipError_t launch_step(int storage, const void *args, int n_items, int waves, int cols, int npl,
-                       bool variants, hipStream_t s);
+hipError_t launch_step(int storage, const void *args, int n_items, const TileShape &t, bool variants,
+                       hipStream_t s);
 hipError_t launch_read(int storage, const void *args, int dom, int nx, int ny, uint32_t which,
                        double *out, hipStream_t s);
 hipError_t launch_mass(int storage, const void *args, int n_doms, const int *dom_nodes_begin,

@@ -397,6 +397,22 @@ __device__ __forceinline__ void add_pull(int a, AT f, AT c, AT vx, AT vy, AT &rR
     tot = tot + f;
 }
 
+// Densities of a node that pulls every population from a fluid neighbour.
+template <class AT, class ColourFn>
+__device__ __forceinline__ void gather_interior(ParC<AT> &P, const AT d[9], AT &rR, AT &rB, ColourFn colour) {
+#pragma clang fp contract(on)
+    AT c, vx, vy;
+    colour(0, c, vx, vy);
+    AT tot = P.w_rest + d[0];
+    rR = c * tot;
+#pragma unroll
+    for (int a = 1; a < 9; a++) {
+        colour(a, c, vx, vy);
+        add_pull(a, (a < 5 ? P.w_axis : P.w_diag) + d[a], c, vx, vy, rR, tot);
+    }
+    rB = tot - rR;
+}
+
 // Completes the post-streaming populations d[] of fluid node (x, y) whose interior pulls are
 // already in d[] (and whose own-node snapshot values are in d[] in snapshot mode): half-way
 // bounce-back on links from solid nodes, Zou-He inlet and convective outlet unknowns; and
@@ -426,15 +442,7 @@ __device__ __forceinline__ void finish_gather(const StepArgs<T, AT> &A, DomC &D,
         rB = tot - rR;
     } else if ((m & 0xFFu) == 0u && !nb.lo && !nb.hi) {
         // interior node: every population is pulled from a fluid neighbour
-        AT tot = wr[0] + d[0];
-        rR = cself * tot;
-#pragma unroll
-        for (int a = 1; a < 9; a++) {
-            AT c, vx, vy;
-            colour(a, c, vx, vy);
-            add_pull(a, wr[a < 5 ? 1 : 2] + d[a], c, vx, vy, rR, tot);
-        }
-        rB = tot - rR;
+        gather_interior(P, d, rR, rB, colour);
     } else {
         if (!BOUNCED) {
 #pragma unroll
@@ -1135,6 +1143,336 @@ __global__ __launch_bounds__(TILE_LANES *R *C, sizeof(typename Codec<T>::AT) == 
         iteration(r + R, std::integral_constant<int, 1>());
         if (r + 2 * R >= y1) break;
     }
+}
+
+// ------------------------------------------------------- the step kernel of short work items
+// A whole work item at once instead of a march: the block holds the item's output rows and four
+// halo rows on each side, NW wavefronts of K rows each, and takes every stage once, with a
+// barrier between stages.  The march needs (rows + 10) / 4 iterations of all five stages in
+// sequence, each waiting for its loads and barriers; here the loads of all rows are in flight
+// together and the stages follow each other once.  Populations are pulled without waiting for the
+// class word; a wavefront whose rows touch a wall then loads the bounced ones.  Node arithmetic
+// and results are step_kernel's, bit for bit.
+//
+// 16 wavefronts of one row (8 output rows): the shortest time of one block, for small lattices.
+// With FP32 arithmetic 16 of two rows (24 output rows of 32), held to 64 registers so that two
+// blocks share a CU, one loading while the other computes; with FP64 arithmetic, where two rows
+// need 118 registers, two blocks of 8 wavefronts of two rows do the same for 8 output rows.
+template <class T, int NW, int K, bool WV>
+__global__ __launch_bounds__(TILE_LANES *NW, sizeof(typename Codec<T>::AT) == 4 ? 8 : 4) void patch_kernel(const StepArgs<T, typename Codec<T>::AT> A) {
+    using AT = typename Codec<T>::AT;
+    constexpr int TX = TILE_LANES, TY = NW * K, H = PATCH_HALO;
+    constexpr int CW = TX + 2, CH = TY + 2;  // colour state: one more column and row per side
+    constexpr uint32_t SB = sizeof(T), CB = sizeof(AT);
+    __shared__ AT s_c[CH * CW], s_vx[CH * CW], s_vy[CH * CW], s_rn[TY * TX];
+    __shared__ int s_wall[NW];
+    // normals take the place of v, which is dead after stage A
+    AT *const s_nx = s_vx, *const s_ny = s_vy;
+
+    const WorkItem *itp = A.items + item_of_block(blockIdx.x, A.n_items);
+    const int dom = __builtin_amdgcn_readfirstlane(itp->dom);
+    const int x0 = __builtin_amdgcn_readfirstlane(itp->x0);
+    const int y0 = __builtin_amdgcn_readfirstlane(itp->y0), y1 = __builtin_amdgcn_readfirstlane(itp->y1);
+    DomC &D = *(DomC *)(A.doms + dom);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / TX), lane = threadIdx.x % TX;
+    const int base = x0 - H, X = base + lane;
+    const int nx_ = D.nx, ny_ = D.ny;
+    const bool open_x = D.open_x != 0;
+    const int xe = open_x ? min(max(X, 0), nx_ - 1) : wrap(X, nx_);
+    const bool edge_item = open_x && (base < 0 || base + TX > nx_);
+    const bool beyond = open_x && xe != X;  // takes the edge column's stencil values
+    const int edge_lane = beyond ? xe - base : lane;
+    const int row0 = w * K;                      // first tile row of the wavefront
+    const int ya = y0 - H + row0;                // and its lattice row, not wrapped
+    const int kn0 = row0 * TX + lane;            // its node in the stencil arrays
+    const int kc0 = (row0 + 1) * CW + lane + 1;  // and in the colour arrays
+    const bool need = ya <= y1 + H;              // the wavefront holds a row that the item needs
+    // lattice rows ya - 1 .. ya + K, periodic, and their first node
+    uint32_t rows[K + 2];
+    {
+        const uint32_t off = (uint32_t)D.off;
+        int yw = wrap(ya - 1, ny_);
+#pragma unroll
+        for (int k = 0; k < K + 2; k++) {
+            rows[k] = off + (uint32_t)yw * (uint32_t)nx_;
+            yw = yw + 1 == ny_ ? 0 : yw + 1;
+        }
+    }
+    const uint32_t FP = A.f_plane_bytes, CP = A.c_plane_bytes;
+
+    // ---- loads of the whole patch: class words, colour state, pulled populations
+    uint32_t m[K];
+    T f[K][9];
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+        m[k] = SELF_SOLID;
+#pragma unroll
+        for (int a = 0; a < 9; a++) f[k][a] = T{};
+    }
+    {
+        const Rsrc c_in = make_rsrc(A.cin, 3 * A.c_plane_bytes);
+        AT c0[K], vx0[K], vy0[K];
+        // the ring of colour state around the tile: rows -1 and TY, then columns -1 and TX
+        constexpr int RING = 2 * CW + 2 * TY;
+        static_assert(RING <= TX * NW, "one ring node per thread");
+        const int t = threadIdx.x;
+        const int rk = t - 2 * CW;
+        const int ry = t < 2 * CW ? (t < CW ? -1 : TY) : rk % TY;
+        const int rx = t < 2 * CW ? (t < CW ? t : t - CW) - 1 : (rk < TY ? -1 : TX);
+        AT c1 = AT(0), vx1 = AT(0), vy1 = AT(0);
+        if (need) {
+            const Rsrc r_mask = make_rsrc(A.mask, (uint32_t)A.plane * 2u);
+#pragma unroll
+            for (int k = 0; k < K; k++) {
+                const uint32_t self = rows[k + 1] + (uint32_t)xe;
+                m[k] = Buf<uint16_t>::load(r_mask, self * 2u, 0);
+                c0[k] = Buf<AT>::load(c_in, self * CB, 0);
+                vx0[k] = Buf<AT>::load(c_in, self * CB, CP);
+                vy0[k] = Buf<AT>::load(c_in, self * CB, 2 * CP);
+            }
+        }
+        if (w <= (RING - 1) / TX) {
+            const int xg = open_x ? min(max(base + rx, 0), nx_ - 1) : wrap(base + rx, nx_);
+            const bool ring = t < RING && y0 - H + ry <= y1 + H;
+            const uint32_t vg = ring ? ((uint32_t)D.off + (uint32_t)wrap(y0 - H + ry, ny_) * (uint32_t)nx_ + (uint32_t)xg) * CB
+                                     : NOWHERE;
+            c1 = Buf<AT>::load(c_in, vg, 0);
+            vx1 = Buf<AT>::load(c_in, vg, CP);
+            vy1 = Buf<AT>::load(c_in, vg, 2 * CP);
+        }
+        if (need) {
+            const Rsrc f_in = make_rsrc(A.fin, A.f_set_bytes);
+            // columns x - 1, x, x + 1; a snapshot state is read at the node itself
+            uint32_t col[3] = {(uint32_t)xe, (uint32_t)xe, (uint32_t)xe};
+            if (!A.own) {
+                col[0] = xe == 0 ? (open_x ? 0u : (uint32_t)nx_ - 1u) : (uint32_t)xe - 1u;
+                col[2] = xe == nx_ - 1 ? (open_x ? (uint32_t)xe : 0u) : (uint32_t)xe + 1u;
+            }
+#pragma unroll
+            for (int k = 0; k < K; k++)
+#pragma unroll
+                for (int a = 0; a < 9; a++) {
+                    const uint32_t row = A.own ? rows[k + 1] : rows[k + 1 - EY[a]];
+                    f[k][a] = Buf<T>::load(f_in, (row + col[1 - EX[a]]) * SB, (uint32_t)a * FP);
+                }
+#pragma unroll
+            for (int k = 0; k < K; k++) {
+                const int kc = kc0 + k * CW;
+                s_c[kc] = c0[k];
+                s_vx[kc] = vx0[k];
+                s_vy[kc] = vy0[k];
+            }
+        }
+        if (t < RING) {
+            const int k = (ry + 1) * CW + rx + 1;
+            s_c[k] = c1;
+            s_vx[k] = vx1;
+            s_vy[k] = vy1;
+        }
+    }
+    // bounced populations and wall normals, where a row has any
+    Pair<AT> wn[K];
+    uint32_t any_m = 0;
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+        if (ya + k >= y1 + H) m[k] = SELF_SOLID;
+        any_m |= m[k];
+        wn[k] = Pair<AT>{AT(0), AT(0)};
+    }
+    const bool wall = __builtin_amdgcn_ballot_w64((any_m & SOLID_BND) != 0) != 0;
+    if (__builtin_amdgcn_ballot_w64((any_m & (SELF_SOLID | 0xFFu)) != 0) != 0) {
+        const Rsrc f_in = make_rsrc(A.fin, A.f_set_bytes), r_ns = make_rsrc(A.ns, A.ns_bytes);
+#pragma unroll
+        for (int k = 0; k < K; k++) {
+            const bool near = !beyond && (m[k] & FLUID_BND);
+            if (__builtin_amdgcn_ballot_w64(near) == 0) continue;
+            const uint32_t self = rows[k + 1] + (uint32_t)xe;
+            wn[k] = load_pair(r_ns, near ? self * (2 * CB) : NOWHERE, AT());
+            const bool lo = open_x && xe == 0, hi = open_x && xe == nx_ - 1;
+            T fb[9];
+            bool bounce[9];
+#pragma unroll
+            for (int a = 1; a < 9; a++) {
+                const bool outside = (EX[a] == 1 && lo) || (EX[a] == -1 && hi);
+                bounce[a] = near && !A.own && (m[k] & (1u << (OPP[a] - 1))) && !outside;
+                fb[a] = Buf<T>::load(f_in, bounce[a] ? self * SB : NOWHERE, (uint32_t)OPP[a] * FP);
+            }
+#pragma unroll
+            for (int a = 1; a < 9; a++) f[k][a] = bounce[a] ? fb[a] : f[k][a];
+        }
+    }
+    __syncthreads();
+
+    // ---- A: gather, densities, colour indicator
+    AT d[K][9], rR[K], rB[K];
+    {
+#pragma unroll
+        for (int k = 0; k < K; k++) {
+#pragma unroll
+            for (int a = 0; a < 9; a++) d[k][a] = Codec<T>::decode(f[k][a], a);
+            rR[k] = rB[k] = AT(0);
+        }
+        const auto colour_at = [&](int k) {
+            return [&, k](int a, AT &c, AT &vx, AT &vy) {
+                const int q = kc0 + (k - EY[a]) * CW - EX[a];
+                c = s_c[q];
+                vx = s_vx[q];
+                vy = s_vy[q];
+            };
+        };
+        if (need) {
+#pragma unroll
+            for (int k = 0; k < K; k++) {
+                AT rn = AT(0);
+                if (!beyond && !(m[k] & SELF_SOLID)) {
+                    const int yw = wrap(ya + k, ny_);
+                    const Nbr nb = make_nbr(D, xe, yw);
+                    finish_gather<true>(A, D, xe, yw, m[k], nb, !A.diag, d[k], rR[k], rB[k], colour_at(k));
+                    rn = colour_indicator(rR[k], rB[k]);
+                }
+                if (edge_item) rn = __shfl(rn, edge_lane);
+                s_rn[kn0 + k * TX] = rn;
+            }
+        }
+    }
+    if (lane == 0) s_wall[w] = wall;
+    __syncthreads();
+    const bool any_wall = __builtin_amdgcn_ballot_w64(lane < NW && s_wall[lane % NW] != 0) != 0;
+
+    // ---- B: virtual colour indicator on outermost solid nodes (Eq. 29)
+    if (any_wall) {
+        if (wall) {
+            const bool surface_energy = WV && (D.wetting & WET_SURFACE_ENERGY);
+#pragma unroll
+            for (int k = 0; k < K; k++) {
+                const int r = row0 + k, kn = kn0 + k * TX;
+                if (r < 1 || r >= TY - 1) continue;
+                AT rn = AT(0);
+                if ((m[k] & SOLID_BND) && lane >= 1 && lane < TX - 1) {
+                    if (surface_energy) rn = par(D, AT()).cos_t;
+                    else rn = fluid_mean<AT>(m[k], [&](int ex, int ey) { return s_rn[kn + ey * TX + ex]; });
+                }
+                if (edge_item) rn = __shfl(rn, edge_lane);
+                if (m[k] & SOLID_BND) s_rn[kn] = rn;
+            }
+        }
+        __syncthreads();
+    }
+
+    // ---- C: colour gradient (Eq. 28), wetting correction, interface normal (Eq. 22), on the
+    // rows that E and D read
+    AT g[K];
+#pragma unroll
+    for (int k = 0; k < K; k++) g[k] = AT(0);
+    if (row0 + K > 2 && row0 < TY - 2 && ya < y1 + 2) {
+        ParC<AT> &P = par(D, AT());
+        const AT eps = P.eps;
+        const bool surface_energy = WV && (D.wetting & WET_SURFACE_ENERGY);
+#pragma unroll
+        for (int k = 0; k < K; k++) {
+            const int r = row0 + k, kn = kn0 + k * TX, y = ya + k;
+            if (r < 2 || r >= TY - 2) continue;
+            AT nx = AT(0), ny = AT(0);
+            if (!(m[k] & SELF_SOLID) && lane >= 2 && lane < TX - 2) {
+                AT gx, gy;
+                const auto rn_at = [&](int ex, int ey) { return s_rn[kn + ey * TX + ex]; };
+                if (m[k] & FLUID_BND) wall_gradient(rn_at, gx, gy);
+                else gradient(rn_at, gx, gy);
+                // contact-line list: each node is recorded by the patch that outputs it
+                if (A.diag && A.cl_count != nullptr && dom == A.cl_dom && (m[k] & FLUID_BND) &&
+                    lane >= H && lane < TX - H && X < nx_ && y >= y0 && y < y1 &&
+                    fsqrt(gx * gx + gy * gy) > eps) {
+                    const int q = atomicAdd(A.cl_count, 1);
+                    if (q < A.cl_cap) A.cl_list[q] = y * nx_ + X;
+                }
+                if ((m[k] & FLUID_BND) && !surface_energy)
+                    wetting_correct(wn[k].x, wn[k].y, P.cos_t, P.sin_t, eps, gx, gy);
+                unit_normal(gx, gy, eps, g[k], nx, ny);
+            }
+            if (edge_item) {
+                nx = __shfl(nx, edge_lane);
+                ny = __shfl(ny, edge_lane);
+            }
+            s_nx[kn] = nx;
+            s_ny[kn] = ny;
+        }
+    }
+    __syncthreads();
+
+    // ---- D: virtual interface normals on outermost solid nodes (Eq. 29, second BC)
+    const bool scheme_b = WV && (D.wetting & WET_SCHEME_B);
+    if (any_wall && !scheme_b) {
+        if (wall) {
+#pragma unroll
+            for (int k = 0; k < K; k++) {
+                const int r = row0 + k, kn = kn0 + k * TX;
+                if (r < 3 || r >= TY - 3) continue;
+                AT vx = AT(0), vy = AT(0);
+                if ((m[k] & SOLID_BND) && lane >= 3 && lane < TX - 3)
+                    fluid_mean2(m[k], [&](int ex, int ey, AT &x, AT &y_) {
+                        x = s_nx[kn + ey * TX + ex];
+                        y_ = s_ny[kn + ey * TX + ex];
+                    }, vx, vy);
+                if (edge_item) {
+                    vx = __shfl(vx, edge_lane);
+                    vy = __shfl(vy, edge_lane);
+                }
+                if (m[k] & SOLID_BND) {
+                    s_nx[kn] = vx;
+                    s_ny[kn] = vy;
+                }
+            }
+        }
+        __syncthreads();
+    }
+
+    // ---- E: curvature (Eq. 13), force (Eq. 10), collision, recolouring state (Eq. 14).  Lanes
+    // without an output node store to NOWHERE.
+    if (ya + K <= y0 || ya >= y1) return;
+    ParC<AT> &P = par(D, AT());
+    // a diagnostic launch writes no state (zero extents drop every store) but (u_x, u_y), through
+    // the colour-state stores, whose two-plane extent then drops the third
+    const Rsrc f_out = make_rsrc(A.fout, A.diag ? 0u : A.f_set_bytes);
+    const Rsrc c_out = A.diag ? make_rsrc(A.u_out, 2 * A.c_plane_bytes) : make_rsrc(A.cout, 3 * A.c_plane_bytes);
+    const bool out_lane = lane >= H && lane < TX - H && X < nx_;
+    bool bad = false;
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+        if (K > 1 && (ya + k < y0 || ya + k >= y1)) continue;
+        const int kn = kn0 + k * TX;
+        const bool out = out_lane && !(m[k] & SELF_SOLID);
+        const auto n_at = [&](int ex, int ey, AT &x, AT &y_) {
+            x = s_nx[kn + ey * TX + ex];
+            y_ = s_ny[kn + ey * TX + ex];
+        };
+        AT dxnx, dynx, dxny, dyny, nx, ny;
+        n_at(0, 0, nx, ny);
+        gradient([&](int ex, int ey) { return s_nx[kn + ey * TX + ex]; }, dxnx, dynx);
+        gradient([&](int ex, int ey) { return s_ny[kn + ey * TX + ex]; }, dxny, dyny);
+        if (WV && scheme_b && out && (m[k] & FLUID_BND)) one_sided_gradient(m[k], n_at, dxnx, dynx, dxny, dyny);
+        AT Fx, Fy, o[9], ux, uy, c, bx, by;
+        csf_force(P.half_sigma, g[k], nx, ny, dxnx, dynx, dxny, dyny, Fx, Fy);
+        collide(P, d[k], Fx, Fy, s_rn[kn], rR[k], rB[k], nx, ny, o, ux, uy, c, bx, by);
+        bad = bad || (out && !isfinite(rR[k] + rB[k] + ux + uy));  // any NaN or overflow
+        if (A.diag) {
+            c = ux;
+            bx = uy;
+        }
+        const uint32_t self = rows[k + 1] + (uint32_t)xe;
+        const uint32_t vf = out ? self * SB : NOWHERE, vc = out ? self * CB : NOWHERE;
+        const uint32_t rb = sizeof(T) == 2 ? round_bits((self - (uint32_t)D.off) * SB, o[0]) : 0u;
+#pragma unroll
+        for (int a = 0; a < 9; a++) {
+            if constexpr (sizeof(T) == 2)
+                store_lo16(f_out, vf, (uint32_t)a * FP, Codec<T>::encode_sr(o[a], a, rb));
+            else
+                Buf<T>::store(f_out, vf, (uint32_t)a * FP, Codec<T>::encode(o[a], a));
+        }
+        Buf<AT>::store(c_out, vc, 0, c);
+        Buf<AT>::store(c_out, vc, CP, bx);
+        Buf<AT>::store(c_out, vc, 2 * CP, by);
+    }
+    if (bad) atomicOr(A.flag, 1);
 }
 
 // --------------------------------------------------- the step kernel with two columns per lane
@@ -1938,22 +2276,34 @@ __global__ __launch_bounds__(DIAG_THREADS) void crossing_kernel(
 }
 
 // ------------------------------------------------------------------- launchers
+constexpr int PATCH64_SINGLE_ROW_ITEMS = 512;
 template <class T, bool WV>
-static hipError_t step_t(const void *args, int n_items, int waves, int cols, int npl, hipStream_t s) {
+static hipError_t step_t(const void *args, int n_items, const TileShape &t, hipStream_t s) {
     const auto &A = *static_cast<const StepArgs<T, typename Codec<T>::AT> *>(args);
     if constexpr (sizeof(typename Codec<T>::AT) == 4) {
-        if (npl == 2) {
-            if (waves == 8)
+        if (t.npl == 2) {
+            if (t.waves == 8)
                 hipLaunchKernelGGL((pair_kernel<T, 8, WV>), dim3(n_items), dim3(TILE_LANES * 8), 0, s, A);
             else
                 hipLaunchKernelGGL((pair_kernel<T, 4, WV>), dim3(n_items), dim3(TILE_LANES * 4), 0, s, A);
             return hipGetLastError();
         }
     }
-    if (npl != 1) return hipErrorInvalidValue;
-    if (cols == 2)
+    if (t.npl != 1) return hipErrorInvalidValue;
+    constexpr bool f64 = sizeof(typename Codec<T>::AT) == 8;
+    if (t.patch(f64)) {
+        // FP64: 16 wavefronts of one row while there are at most two blocks for each of the 256 CUs
+        // (234 items 10.6 us a step), then 8 of two rows (4224 items 113 us, and 127 with the other)
+        if (f64 && n_items > PATCH64_SINGLE_ROW_ITEMS)
+            hipLaunchKernelGGL((patch_kernel<T, 8, 2, WV>), dim3(n_items), dim3(TILE_LANES * 8), 0, s, A);
+        else if (f64 || t.chunk == PATCH_ROWS)
+            hipLaunchKernelGGL((patch_kernel<T, 16, 1, WV>), dim3(n_items), dim3(TILE_LANES * 16), 0, s, A);
+        else
+            hipLaunchKernelGGL((patch_kernel<T, f64 ? 8 : 16, 2, WV>), dim3(n_items), dim3(TILE_LANES * (f64 ? 8 : 16)), 0, s, A);
+    }
+    else if (t.cols == 2)
         hipLaunchKernelGGL((step_kernel<T, 4, 2, WV>), dim3(n_items), dim3(TILE_LANES * 8), 0, s, A);
-    else if (waves == 8)
+    else if (t.waves == 8)
         hipLaunchKernelGGL((step_kernel<T, 8, 1, WV>), dim3(n_items), dim3(TILE_LANES * 8), 0, s, A);
     else
         hipLaunchKernelGGL((step_kernel<T, 4, 1, WV>), dim3(n_items), dim3(TILE_LANES * 4), 0, s, A);
@@ -1961,20 +2311,18 @@ static hipError_t step_t(const void *args, int n_items, int waves, int cols, int
 }
 
 template <class T>
-static hipError_t step_v(const void *args, int n_items, int waves, int cols, int npl, bool variants,
-                         hipStream_t s) {
-    return variants ? step_t<T, true>(args, n_items, waves, cols, npl, s)
-                    : step_t<T, false>(args, n_items, waves, cols, npl, s);
+static hipError_t step_v(const void *args, int n_items, const TileShape &t, bool variants, hipStream_t s) {
+    return variants ? step_t<T, true>(args, n_items, t, s) : step_t<T, false>(args, n_items, t, s);
 }
 
-hipError_t launch_step(int storage, const void *args, int n_items, int waves, int cols, int npl,
-                       bool variants, hipStream_t s) {
+hipError_t launch_step(int storage, const void *args, int n_items, const TileShape &t, bool variants,
+                       hipStream_t s) {
     if (n_items <= 0) return hipSuccess;
     switch (storage) {
-        case 0: return step_v<double>(args, n_items, waves, cols, npl, variants, s);
-        case 1: return step_v<float>(args, n_items, waves, cols, npl, variants, s);
-        case 2: return step_v<__half>(args, n_items, waves, cols, npl, variants, s);
-        case 3: return step_v<C16>(args, n_items, waves, cols, npl, variants, s);
+        case 0: return step_v<double>(args, n_items, t, variants, s);
+        case 1: return step_v<float>(args, n_items, t, variants, s);
+        case 2: return step_v<__half>(args, n_items, t, variants, s);
+        case 3: return step_v<C16>(args, n_items, t, variants, s);
     }
     return hipErrorInvalidValue;
 }
