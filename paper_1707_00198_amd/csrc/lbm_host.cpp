@@ -446,12 +446,12 @@ constexpr int DEFAULT_COLS = 1;
 // against the best march):
 //  FP32 arithmetic, binary16 / FP32 storage: items of 8 rows up to 1536 of them (234 items 8.3
 //    against 20, 1404 items 20.4 against 33; 1600 items 24 where items of 24 rows take 20), then
-//    items of 24 rows: 44 channels 630 x 60 44 / 45 against 64, 16384 x 512 183 / 226 against
-//    190 / 250.  In the 16-bit storages only up to 8192 items (60 channels of the sweep, 12240
-//    items: 335 against 327 in 64-row marches); an FP32 step is bound by HBM there and gains.
+//    items of 24 rows: 44 channels 630 x 60 42 / 45 against 63, 16384 x 512 177 / 218 against
+//    186 / 250, 60 channels of the sweep (12240 items) 321 / 369 against 325 / 406.  In the
+//    16-bit storages only up to 16384 items: the gain is gone there; FP32 is bound by HBM.
 //  FP64: items of 8 rows up to 10240 (234 items 10.6 against 21.7, 4224 items 113 against 119,
 //    9669 items 242 against 248; 19338 items 441 against 411).
-constexpr size_t PATCH_ITEMS = 1536, PATCH_TALL_ITEMS_16 = 8192, PATCH_ITEMS_F64 = 10240;
+constexpr size_t PATCH_ITEMS = 1536, PATCH_TALL_ITEMS_16 = 16384, PATCH_ITEMS_F64 = 10240;
 TileShape builtin_tile(const std::vector<lbm_domain_desc> &d, int storage) {
     const TileShape patch{PATCH_ROWS, 8, 1, 1}, tall{PATCH_TALL_ROWS, 8, 1, 1};
     if (build_items(d, patch, storage).size() <= (storage == 0 ? PATCH_ITEMS_F64 : PATCH_ITEMS)) return patch;

@@ -385,31 +385,39 @@ __device__ __forceinline__ bool pull_outside(const Nbr &n, int a) {
 
 // Adds the population f that direction a pulls from a node of colour state (c, v) to the red
 // density (c f + w_a e_a . v, Eq. 14) and to the total.  The total takes the same steps as the
-// red density, so where every source is pure red (c = 1, v = 0) the two stay equal.
+// red density, so where every source is pure red (c = 1, v = 0) the two stay equal.  The sums
+// run from the smallest populations to the largest (diagonal, axis, rest): the partial sums, and
+// with them the rounding errors of the colour split, then stay small for longest.
 template <class AT>
 __device__ __forceinline__ void add_pull(int a, AT f, AT c, AT vx, AT vy, AT &rR, AT &tot) {
 #pragma clang fp contract(on)
     const AT ev = EX[a] == 0 ? (EY[a] > 0 ? vy : -vy)
                              : (EY[a] == 0 ? (EX[a] > 0 ? vx : -vx)
                                            : (EX[a] > 0 ? vx : -vx) + (EY[a] > 0 ? vy : -vy));
-    rR = c * f + rR;
-    rR = wgt<AT>(a) * ev + rR;
+    const AT p = wgt<AT>(a) * ev;
+    const AT r = c * f + p;
+    rR = rR + r;
     tot = tot + f;
 }
+__device__ constexpr int PULL_ORDER[8] = {5, 6, 7, 8, 1, 2, 3, 4};
 
 // Densities of a node that pulls every population from a fluid neighbour.
 template <class AT, class ColourFn>
 __device__ __forceinline__ void gather_interior(ParC<AT> &P, const AT d[9], AT &rR, AT &rB, ColourFn colour) {
 #pragma clang fp contract(on)
-    AT c, vx, vy;
-    colour(0, c, vx, vy);
-    AT tot = P.w_rest + d[0];
-    rR = c * tot;
+    AT tot = AT(0), c, vx, vy;
+    rR = AT(0);
 #pragma unroll
-    for (int a = 1; a < 9; a++) {
+    for (int k = 0; k < 8; k++) {
+        const int a = PULL_ORDER[k];
         colour(a, c, vx, vy);
         add_pull(a, (a < 5 ? P.w_axis : P.w_diag) + d[a], c, vx, vy, rR, tot);
     }
+    colour(0, c, vx, vy);
+    const AT f0 = P.w_rest + d[0];
+    const AT r0 = c * f0;
+    rR = rR + r0;
+    tot = tot + f0;
     rB = tot - rR;
 }
 
@@ -483,10 +491,10 @@ __device__ __forceinline__ void finish_gather(const StepArgs<T, AT> &A, DomC &D,
         }
         // rho_B as the total minus rho_R: exactly 0 where every source is pure red (c = 1,
         // v = 0), and rho_R exactly 0 where every source is pure blue
-        AT tot = wr[0] + d[0];
-        rR = cself * tot;
+        AT tot = AT(0);
 #pragma unroll
-        for (int a = 1; a < 9; a++) {
+        for (int k = 0; k < 8; k++) {
+            const int a = PULL_ORDER[k];
             const bool outside = pull_outside(nb, a), bounced = (m & (1u << (OPP[a] - 1))) != 0;
             AT c, vx, vy;
             colour(a, c, vx, vy);
@@ -497,6 +505,10 @@ __device__ __forceinline__ void finish_gather(const StepArgs<T, AT> &A, DomC &D,
             vy = outside ? AT(0) : (bounced ? -vys : vy);
             add_pull(a, wr[a < 5 ? 1 : 2] + d[a], c, vx, vy, rR, tot);
         }
+        const AT f0 = wr[0] + d[0];
+        const AT r0 = cself * f0;
+        rR = rR + r0;
+        tot = tot + f0;
         rB = tot - rR;
     }
     if (write_hist && nb.hi) {
