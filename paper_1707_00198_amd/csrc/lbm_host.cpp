@@ -266,7 +266,9 @@ struct lbm_ctx {
     double *diag_host = nullptr;
     int *rows_host = nullptr;
     bool snap_valid = false;
+    bool snap_first = false;  // the snapshot is the first of the two velocity buffers
     int max_fluid_bnd = 0;  // largest number of outermost fluid nodes in one domain
+    size_t max_nodes = 1;   // nodes of the largest domain
     // step graphs: `graph_steps` step launches captured once on a private stream, one graph per
     // parity a replay starts from (graph_steps is even, so a replay ends on the same parity)
     int graph_steps = 0;
@@ -313,29 +315,22 @@ struct AnyArgs {
     alignas(16) unsigned char bytes[sizeof(StepArgs<double, double>)];
 };
 
-// Layout of the diagnostics buffer: velocity (u_x, u_y planes at the colour-plane stride), its
-// snapshot, reduction partials and results, the row list and results of crossings, and the
-// contact-line counter and list (room for every outermost fluid node of the largest domain).
+// Layout of the diagnostics buffer: velocity (u_x, u_y planes at the colour-plane stride) and its
+// snapshot, which change places when a snapshot is taken, reduction partials, and the contact-line
+// counter and list (room for every outermost fluid node of the largest domain).  Results and row
+// lists are in pinned host memory, which the kernels access directly.
 struct DiagLayout {
-    size_t u = 0, snap = 0, part = 0, res = 0, rows = 0, cross = 0, cl_count = 0, cl_list = 0,
-           bytes = 0;
+    size_t u = 0, snap = 0, part = 0, cl_count = 0, cl_list = 0, bytes = 0;
 };
 DiagLayout diag_layout(const lbm_ctx *c) {
     DiagLayout D;
     const size_t cp = c->L.vx_off - c->L.c_off;
     size_t o = 0;
-    D.u = o;
-    o += 2 * cp;
-    D.snap = o;
-    o += 2 * cp;
+    D.u = c->snap_first ? 2 * cp : 0;
+    D.snap = c->snap_first ? 0 : 2 * cp;
+    o += 4 * cp;
     D.part = o;
     o += align_up(std::max<size_t>((size_t)c->n * DIAG_BLOCKS * 2, DIAG_BLOCKS * 4) * sizeof(double), 256);
-    D.res = o;
-    o += align_up(std::max<size_t>(2 * (size_t)c->n, 4) * sizeof(double), 256);
-    D.rows = o;
-    o += align_up(DIAG_MAX_ROWS * sizeof(int), 256);
-    D.cross = o;
-    o += align_up(DIAG_MAX_ROWS * sizeof(double), 256);
     D.cl_count = o;
     o += 256;
     D.cl_list = o;
@@ -663,7 +658,10 @@ int lbm_create(const lbm_domain_desc *domains, int n, int storage, void *state_d
     c->noalloc = noalloc;
     c->n = n;
     c->storage = storage;
-    for (int i = 0; i < n; i++) c->variants = c->variants || domains[i].wetting != 0;
+    for (int i = 0; i < n; i++) {
+        c->variants = c->variants || domains[i].wetting != 0;
+        c->max_nodes = std::max(c->max_nodes, (size_t)domains[i].nx * domains[i].ny);
+    }
     c->stream = (hipStream_t)hip_stream;
     c->state = (char *)state_dev;
     c->scratch = (char *)scratch_dev;
@@ -872,12 +870,9 @@ int lbm_mass(lbm_ctx *c, double *out_host) {
     if (!c || !out_host) return fail(LBM_EINVAL, "null argument");
     AnyArgs a = make_args(c, c->parity);
     double *partials = reinterpret_cast<double *>(c->scratch + c->L.partials);
-    double *mout = reinterpret_cast<double *>(c->scratch + c->L.mass_out);
-    HIP_OK(launch_mass(c->storage, a.bytes, c->n, nullptr, partials, c->L.bpd, mout, c->stream));
-    HIP_OK(hipMemcpyAsync(c->mass_host, mout, 2 * (size_t)c->n * sizeof(double),
-                          hipMemcpyDeviceToHost, c->stream));
-    HIP_OK(hipMemcpyAsync(c->flag_host, c->scratch + c->L.flag, sizeof(int), hipMemcpyDeviceToHost,
-                          c->stream));
+    // no more blocks per domain than the largest one fills
+    const int bpd = (int)std::min<size_t>(c->L.bpd, (c->max_nodes + 255) / 256);
+    HIP_OK(launch_mass(c->storage, a.bytes, c->n, partials, bpd, c->mass_host, c->flag_host, c->stream));
     HIP_OK(hipStreamSynchronize(c->stream));
     std::memcpy(out_host, c->mass_host, 2 * (size_t)c->n * sizeof(double));
     if (*c->flag_host) return fail(LBM_ENONFINITE, "a non-finite density or velocity appeared");
@@ -958,7 +953,7 @@ size_t lbm_diag_bytes(const lbm_ctx *c) { return c ? diag_layout(c).bytes : 0; }
 int lbm_diag_attach(lbm_ctx *c, void *diag_dev, size_t bytes) {
     if (!c) return fail(LBM_EINVAL, "null context");
     HIP_OK(hipStreamSynchronize(c->stream));
-    c->snap_valid = false;
+    c->snap_valid = c->snap_first = false;
     if (!diag_dev) {
         c->diag = nullptr;
         return LBM_OK;
@@ -982,20 +977,16 @@ int lbm_diag_velocity(lbm_ctx *c, int snapshot, double *out_host) {
     const DiagLayout DL = diag_layout(c);
     AnyArgs da = make_diag_args(c);
     HIP_OK(launch_step(c->storage, da.bytes, (int)c->items.size(), c->tile, c->variants, c->stream));
-    double *res = reinterpret_cast<double *>(c->diag + DL.res);
     HIP_OK(launch_velocity_stats(c->storage, da.bytes, c->n, c->diag + DL.u,
                                  c->snap_valid ? c->diag + DL.snap : nullptr,
-                                 reinterpret_cast<double *>(c->diag + DL.part), res, c->stream));
-    if (snapshot)
-        HIP_OK(hipMemcpyAsync(c->diag + DL.snap, c->diag + DL.u, DL.snap - DL.u, hipMemcpyDeviceToDevice,
-                              c->stream));
-    HIP_OK(hipMemcpyAsync(c->diag_host, res, 2 * (size_t)c->n * sizeof(double), hipMemcpyDeviceToHost,
-                          c->stream));
-    HIP_OK(hipMemcpyAsync(c->flag_host, c->scratch + c->L.flag, sizeof(int), hipMemcpyDeviceToHost,
-                          c->stream));
+                                 reinterpret_cast<double *>(c->diag + DL.part), c->diag_host, c->flag_host,
+                                 c->stream));
     HIP_OK(hipStreamSynchronize(c->stream));
     std::memcpy(out_host, c->diag_host, 2 * (size_t)c->n * sizeof(double));
-    if (snapshot) c->snap_valid = true;
+    if (snapshot) {  // the buffer just written becomes the snapshot
+        c->snap_valid = true;
+        c->snap_first = !c->snap_first;
+    }
     if (*c->flag_host) return fail(LBM_ENONFINITE, "a non-finite density or velocity appeared");
     return LBM_OK;
 }
@@ -1006,10 +997,8 @@ int lbm_diag_region_mass(lbm_ctx *c, int domain, const uint8_t *region_dev, doub
     if (!c->diag) return fail(LBM_ESTATE, "no diagnostics buffer attached (lbm_diag_attach)");
     const DiagLayout DL = diag_layout(c);
     AnyArgs a = make_args(c, c->parity);
-    double *res = reinterpret_cast<double *>(c->diag + DL.res);
     HIP_OK(launch_region_mass(c->storage, a.bytes, domain, region_dev,
-                              reinterpret_cast<double *>(c->diag + DL.part), res, c->stream));
-    HIP_OK(hipMemcpyAsync(c->diag_host, res, 4 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+                              reinterpret_cast<double *>(c->diag + DL.part), c->diag_host, c->stream));
     HIP_OK(hipStreamSynchronize(c->stream));
     std::memcpy(out_host, c->diag_host, 4 * sizeof(double));
     return LBM_OK;
@@ -1023,14 +1012,10 @@ int lbm_diag_crossings(lbm_ctx *c, int domain, const int32_t *rows_host, int n_r
     for (int k = 0; k < n_rows; k++)
         if (rows_host[k] < 0 || rows_host[k] >= c->desc[domain].ny)
             return fail(LBM_EINVAL, "row %d outside the domain", rows_host[k]);
-    const DiagLayout DL = diag_layout(c);
     std::memcpy(c->rows_host, rows_host, (size_t)n_rows * sizeof(int));
-    int *rows = reinterpret_cast<int *>(c->diag + DL.rows);
-    double *out = reinterpret_cast<double *>(c->diag + DL.cross);
-    HIP_OK(hipMemcpyAsync(rows, c->rows_host, (size_t)n_rows * sizeof(int), hipMemcpyHostToDevice, c->stream));
     AnyArgs a = make_args(c, c->parity);
-    HIP_OK(launch_crossings(c->storage, a.bytes, domain, rows, n_rows, out, c->stream));
-    HIP_OK(hipMemcpyAsync(c->diag_host, out, (size_t)n_rows * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+    HIP_OK(launch_crossings(c->storage, a.bytes, domain, c->desc[domain].nx, c->rows_host, n_rows, c->diag_host,
+                            c->stream));
     HIP_OK(hipStreamSynchronize(c->stream));
     std::memcpy(out_host, c->diag_host, (size_t)n_rows * sizeof(double));
     return LBM_OK;
@@ -1052,7 +1037,7 @@ int lbm_diag_crossings_noalloc(lbm_ctx *c, int domain, const int32_t *rows_host,
     HIP_OK(hipMemcpyAsync(c->noalloc, rows_host, (size_t)n_rows * sizeof(int32_t), hipMemcpyHostToDevice,
                           c->stream));
     AnyArgs a = make_args(c, c->parity);
-    HIP_OK(launch_crossings_noalloc(c->storage, a.bytes, domain, c->noalloc, n_rows, c->stream));
+    HIP_OK(launch_crossings_noalloc(c->storage, a.bytes, domain, c->desc[domain].nx, c->noalloc, n_rows, c->stream));
     HIP_OK(hipMemcpyAsync(out_host, static_cast<char *>(c->noalloc) + NOALLOC_OUT_OFFSET,
                           (size_t)n_rows * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     HIP_OK(hipStreamSynchronize(c->stream));

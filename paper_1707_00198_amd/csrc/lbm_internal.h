@@ -130,15 +130,17 @@ hipError_t launch_step(int storage, const void *args, int n_items, const TileSha
                        hipStream_t s);
 hipError_t launch_read(int storage, const void *args, int dom, int nx, int ny, uint32_t which,
                        double *out, hipStream_t s);
-hipError_t launch_mass(int storage, const void *args, int n_doms, const int *dom_nodes_begin,
-                       double *partials, int n_blocks_per_dom, double *out, hipStream_t s);
+// `out` and `flag_out` (the non-finite flag) may be pinned host memory, here and below.
+hipError_t launch_mass(int storage, const void *args, int n_doms, double *partials, int n_blocks_per_dom,
+                       double *out, int *flag_out, hipStream_t s);
 
 // Diagnostics (lbm_kernels.hip).
 constexpr int DIAG_BLOCKS = 64;     // blocks per domain of the diagnostic reductions
 constexpr int DIAG_MAX_ROWS = 4096;  // rows per lbm_diag_crossings call
 // Per domain: |u|max over fluid nodes, and max(|u_x - s_x|, |u_y - s_y|) against the snapshot.
 hipError_t launch_velocity_stats(int storage, const void *args, int n_doms, const void *u,
-                                 const void *snap, double *partials, double *out, hipStream_t s);
+                                 const void *snap, double *partials, double *out, int *flag_out,
+                                 hipStream_t s);
 // u_x, u_y of one domain as FP64 planes (solid nodes 0); either output may be NULL.
 hipError_t launch_velocity_copy(int storage, const void *args, int dom, const void *u,
                                 double *ox, double *oy, hipStream_t s);
@@ -146,7 +148,8 @@ hipError_t launch_velocity_copy(int storage, const void *args, int dom, const vo
 hipError_t launch_region_mass(int storage, const void *args, int dom, const uint8_t *region,
                               double *partials, double *out, hipStream_t s);
 // First x of each listed row where rho^N goes from > 0 to <= 0 (interpolated), NaN if none.
-hipError_t launch_crossings(int storage, const void *args, int dom, const int *rows, int n_rows,
+// `nx` is the domain's width; `rows` may be pinned host memory.
+hipError_t launch_crossings(int storage, const void *args, int dom, int nx, const int *rows, int n_rows,
                             double *out, hipStream_t s);
 
 // Staging of lbm_diag_crossings_noalloc in a static device array (lbm_kernels.hip): up to
@@ -158,7 +161,7 @@ constexpr size_t NOALLOC_SCRATCH_BYTES = NOALLOC_OUT_OFFSET + NOALLOC_ROWS * siz
 // per device with hipGetSymbolAddress and cached.
 hipError_t noalloc_scratch(int device, void **out);
 // crossing_kernel with rows and results in the array at scratch_dev (noalloc_scratch's address).
-hipError_t launch_crossings_noalloc(int storage, const void *args, int dom, void *scratch_dev,
+hipError_t launch_crossings_noalloc(int storage, const void *args, int dom, int nx, void *scratch_dev,
                                     int n_rows, hipStream_t s);
 
 }  // namespace lbmcg

@@ -2021,10 +2021,9 @@ __global__ void read_kernel(const StepArgs<T, typename Codec<T>::AT> A, int dom,
                             double *out) {
     using AT = typename Codec<T>::AT;
     DomC &D = *(DomC *)(A.doms + dom);
-    const size_t nn = (size_t)D.nx * D.ny;
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < nn;
-         i += (size_t)gridDim.x * blockDim.x) {
-        const int x = (int)(i % D.nx), y = (int)(i / D.nx);
+    const uint32_t nn = (uint32_t)D.nx * (uint32_t)D.ny, nx = (uint32_t)D.nx;
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < nn; i += gridDim.x * blockDim.x) {
+        const int x = (int)(i % nx), y = (int)(i / nx);
         const uint32_t m = A.mask[D.off + i];
         double fR[9], fB[9], sR = 0.0, sB = 0.0;
 #pragma unroll
@@ -2074,13 +2073,13 @@ __global__ void read_kernel(const StepArgs<T, typename Codec<T>::AT> A, int dom,
             }
         }
         size_t p = 0;
-        if (which & 1u) out[(p++) * nn + i] = sR;
-        if (which & 2u) out[(p++) * nn + i] = sB;
+        if (which & 1u) out[(p++) * (size_t)nn + i] = sR;
+        if (which & 2u) out[(p++) * (size_t)nn + i] = sB;
         if (which & 4u) {
 #pragma unroll
-            for (int a = 0; a < 9; a++) out[(p + a) * nn + i] = fR[a];
+            for (int a = 0; a < 9; a++) out[(p + a) * (size_t)nn + i] = fR[a];
 #pragma unroll
-            for (int a = 0; a < 9; a++) out[(p + 9 + a) * nn + i] = fB[a];
+            for (int a = 0; a < 9; a++) out[(p + 9 + a) * (size_t)nn + i] = fB[a];
         }
     }
 }
@@ -2095,14 +2094,13 @@ __global__ __launch_bounds__(MASS_THREADS) void mass_partial_kernel(
     const int dom = blockIdx.x / blocks_per_dom;
     const int b = blockIdx.x % blocks_per_dom;
     DomC &D = *(DomC *)(A.doms + dom);
-    const size_t nn = (size_t)D.nx * D.ny;
+    const uint32_t nn = (uint32_t)D.nx * (uint32_t)D.ny, nx = (uint32_t)D.nx;
     double sR = 0.0, sB = 0.0;
-    for (size_t i = (size_t)b * MASS_THREADS + threadIdx.x; i < nn;
-         i += (size_t)blocks_per_dom * MASS_THREADS) {
+    for (uint32_t i = (uint32_t)b * MASS_THREADS + threadIdx.x; i < nn; i += (uint32_t)blocks_per_dom * MASS_THREADS) {
         const uint32_t m = A.mask[D.off + i];
         if (m & SELF_SOLID) continue;
         AT d[9], rR, rB;
-        gather_global(A, D, (int)(i % D.nx), (int)(i / D.nx), m, d, rR, rB);
+        gather_global(A, D, (int)(i % nx), (int)(i / nx), m, d, rR, rB);
         sR += (double)rR;
         sB += (double)rB;
     }
@@ -2123,17 +2121,39 @@ __global__ __launch_bounds__(MASS_THREADS) void mass_partial_kernel(
     }
 }
 
-__global__ void mass_final_kernel(const double *partials, int n_doms, int blocks_per_dom,
-                                  double *out) {
-    const int dom = blockIdx.x * blockDim.x + threadIdx.x;
-    if (dom >= n_doms) return;
+// Sum of a value over the block's threads, in a fixed order, in every thread.
+template <int THREADS>
+__device__ __forceinline__ double block_total(double v, double *sh) {
+    sh[threadIdx.x] = v;
+    __syncthreads();
+    for (int k = THREADS / 2; k > 0; k >>= 1) {
+        if ((int)threadIdx.x < k) sh[threadIdx.x] += sh[threadIdx.x + k];
+        __syncthreads();
+    }
+    const double r = sh[0];
+    __syncthreads();
+    return r;
+}
+
+// The final kernels of the reductions take one block per domain: a single thread walking the
+// partial results waits for each of up to 1024 loads in turn (a mass sum of a 64 x 34 lattice
+// took 100 us).  Results and the non-finite flag go straight to the caller's pinned host memory.
+__global__ __launch_bounds__(MASS_THREADS) void mass_final_kernel(const double *partials, int blocks_per_dom,
+                                                                  double *out, const int *flag, int *flag_out) {
+    const int dom = blockIdx.x;
     double sR = 0.0, sB = 0.0;
-    for (int b = 0; b < blocks_per_dom; b++) {
+    for (int b = threadIdx.x; b < blocks_per_dom; b += MASS_THREADS) {
         sR += partials[2 * (dom * blocks_per_dom + b)];
         sB += partials[2 * (dom * blocks_per_dom + b) + 1];
     }
-    out[2 * dom] = sR;
-    out[2 * dom + 1] = sB;
+    __shared__ double sh[MASS_THREADS];
+    sR = block_total<MASS_THREADS>(sR, sh);
+    sB = block_total<MASS_THREADS>(sB, sh);
+    if (threadIdx.x == 0) {
+        out[2 * dom] = sR;
+        out[2 * dom + 1] = sB;
+        if (dom == 0) *flag_out = *flag;
+    }
 }
 
 // ---------------------------------------------------------------- diagnostics (Sec. III)
@@ -2146,18 +2166,6 @@ __device__ __forceinline__ double block_max(double v, double *sh) {
     __syncthreads();
     for (int k = DIAG_THREADS / 2; k > 0; k >>= 1) {
         if ((int)threadIdx.x < k) sh[threadIdx.x] = fmax(sh[threadIdx.x], sh[threadIdx.x + k]);
-        __syncthreads();
-    }
-    const double r = sh[0];
-    __syncthreads();
-    return r;
-}
-
-__device__ __forceinline__ double block_sum(double v, double *sh) {
-    sh[threadIdx.x] = v;
-    __syncthreads();
-    for (int k = DIAG_THREADS / 2; k > 0; k >>= 1) {
-        if ((int)threadIdx.x < k) sh[threadIdx.x] += sh[threadIdx.x + k];
         __syncthreads();
     }
     const double r = sh[0];
@@ -2190,16 +2198,21 @@ __global__ __launch_bounds__(DIAG_THREADS) void velocity_stats_kernel(
     }
 }
 
-__global__ void max_final_kernel(const double *partials, int n_doms, double *out, int has_snap) {
-    const int dom = blockIdx.x * blockDim.x + threadIdx.x;
-    if (dom >= n_doms) return;
-    double a = 0.0, e = 0.0;
-    for (int b = 0; b < DIAG_BLOCKS; b++) {
-        a = fmax(a, partials[2 * (dom * DIAG_BLOCKS + b)]);
-        e = fmax(e, partials[2 * (dom * DIAG_BLOCKS + b) + 1]);
+// one block of DIAG_BLOCKS threads per domain
+__global__ __launch_bounds__(DIAG_BLOCKS) void max_final_kernel(const double *partials, double *out, int has_snap,
+                                                                const int *flag, int *flag_out) {
+    static_assert(DIAG_BLOCKS == TILE_LANES, "one wavefront per domain");
+    const int dom = blockIdx.x;
+    double a = partials[2 * (dom * DIAG_BLOCKS + threadIdx.x)], e = partials[2 * (dom * DIAG_BLOCKS + threadIdx.x) + 1];
+    for (int k = DIAG_BLOCKS / 2; k > 0; k >>= 1) {
+        a = fmax(a, __shfl_down(a, k));
+        e = fmax(e, __shfl_down(e, k));
     }
-    out[2 * dom] = a;
-    out[2 * dom + 1] = has_snap ? e : __builtin_nan("");
+    if (threadIdx.x == 0) {
+        out[2 * dom] = a;
+        out[2 * dom + 1] = has_snap ? e : __builtin_nan("");
+        if (dom == 0) *flag_out = *flag;
+    }
 }
 
 template <class AT>
@@ -2221,30 +2234,30 @@ __global__ __launch_bounds__(DIAG_THREADS) void region_mass_kernel(
     const StepArgs<T, typename Codec<T>::AT> A, int dom, const uint8_t *region, double *partials) {
     using AT = typename Codec<T>::AT;
     DomC &D = *(DomC *)(A.doms + dom);
-    const size_t nn = (size_t)D.nx * D.ny;
+    const uint32_t nn = (uint32_t)D.nx * (uint32_t)D.ny, nx = (uint32_t)D.nx;
     double s[4] = {0.0, 0.0, 0.0, 0.0};
-    for (size_t i = blockIdx.x * (size_t)DIAG_THREADS + threadIdx.x; i < nn; i += (size_t)DIAG_BLOCKS * DIAG_THREADS) {
+    for (uint32_t i = blockIdx.x * DIAG_THREADS + threadIdx.x; i < nn; i += DIAG_BLOCKS * DIAG_THREADS) {
         const uint32_t m = A.mask[D.off + i];
         if (m & SELF_SOLID) continue;
         AT d[9], rR, rB;
-        gather_global(A, D, (int)(i % D.nx), (int)(i / D.nx), m, d, rR, rB);
+        gather_global(A, D, (int)(i % nx), (int)(i / nx), m, d, rR, rB);
         const int k = region[i] ? 0 : 1;
         s[k] += (double)rR;
         s[2 + k] += (double)rB;
     }
     __shared__ double sh[DIAG_THREADS];
     for (int k = 0; k < 4; k++) {
-        const double v = block_sum(s[k], sh);
+        const double v = block_total<DIAG_THREADS>(s[k], sh);
         if (threadIdx.x == 0) partials[4 * blockIdx.x + k] = v;
     }
 }
 
-__global__ void sum4_final_kernel(const double *partials, double *out) {
-    const int k = threadIdx.x;
-    if (k >= 4) return;
-    double v = 0.0;
-    for (int b = 0; b < DIAG_BLOCKS; b++) v += partials[4 * b + k];
-    out[k] = v;
+__global__ __launch_bounds__(DIAG_BLOCKS) void sum4_final_kernel(const double *partials, double *out) {
+    __shared__ double sh[DIAG_BLOCKS];
+    for (int k = 0; k < 4; k++) {
+        const double v = block_total<DIAG_BLOCKS>(partials[4 * threadIdx.x + k], sh);
+        if (threadIdx.x == 0) out[k] = v;
+    }
 }
 
 // rho^N of node (x, y) from its gathered densities; 0 on solid nodes
@@ -2259,32 +2272,31 @@ __device__ double rho_n_at(const StepArgs<T, typename Codec<T>::AT> &A, DomC &D,
 }
 
 // One block per listed row: the first x with rho^N(x) > 0 >= rho^N(x + 1), interpolated
-// linearly to x + rho^N(x) / (rho^N(x) - rho^N(x + 1))
+// linearly to x + rho^N(x) / (rho^N(x) - rho^N(x + 1)).  The row is taken in windows of one node
+// per thread, each gathered once and overlapping the next by a node, up to the first crossing.
+constexpr int CROSS_THREADS = 1024;
 template <class T>
-__global__ __launch_bounds__(DIAG_THREADS) void crossing_kernel(
+__global__ __launch_bounds__(CROSS_THREADS) void crossing_kernel(
     const StepArgs<T, typename Codec<T>::AT> A, int dom, const int *rows, double *out) {
     DomC &D = *(DomC *)(A.doms + dom);
-    const int y = rows[blockIdx.x];
+    const int y = rows[blockIdx.x], n = blockDim.x, t = threadIdx.x;
+    __shared__ double rn[CROSS_THREADS];
     __shared__ int first;
-    if (threadIdx.x == 0) first = D.nx;
-    __syncthreads();
-    if (y >= 0 && y < D.ny) {
-        for (int x = threadIdx.x; x < D.nx - 1; x += DIAG_THREADS) {
-            // early exit once some thread has found a crossing further left (an atomic read:
-            // other threads lower the word concurrently; the result is read after the barrier)
-            if (x >= __hip_atomic_load(&first, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) break;
-            if (rho_n_at(A, D, x, y) > 0.0 && rho_n_at(A, D, x + 1, y) <= 0.0) atomicMin(&first, x);
+    if (t == 0) first = n;
+    const int last = y >= 0 && y < D.ny ? D.nx - 1 : 0;
+    for (int x0 = 0; x0 < last; x0 += n - 1) {
+        const int x = x0 + t;
+        rn[t] = x < D.nx ? rho_n_at(A, D, x, y) : 0.0;
+        __syncthreads();
+        const bool cross = t < n - 1 && x < D.nx - 1 && rn[t] > 0.0 && rn[t + 1] <= 0.0;
+        if (cross) atomicMin(&first, t);
+        __syncthreads();
+        if (first < n) {
+            if (t == first) out[blockIdx.x] = x + rn[t] / (rn[t] - rn[t + 1]);
+            return;
         }
     }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double r = __builtin_nan("");
-        if (y >= 0 && y < D.ny && first < D.nx) {
-            const double a = rho_n_at(A, D, first, y), b = rho_n_at(A, D, first + 1, y);
-            r = first + a / (a - b);
-        }
-        out[blockIdx.x] = r;
-    }
+    if (t == 0) out[blockIdx.x] = __builtin_nan("");
 }
 
 // ------------------------------------------------------------------- launchers
@@ -2362,22 +2374,22 @@ hipError_t launch_read(int storage, const void *args, int dom, int nx, int ny, u
 
 template <class T>
 static hipError_t mass_t(const void *args, int n_doms, double *partials, int bpd, double *out,
-                         hipStream_t s) {
+                         int *flag_out, hipStream_t s) {
     const auto &A = *static_cast<const StepArgs<T, typename Codec<T>::AT> *>(args);
     hipLaunchKernelGGL(mass_partial_kernel<T>, dim3(n_doms * bpd), dim3(MASS_THREADS), 0, s, A,
                        bpd, partials);
-    hipLaunchKernelGGL(mass_final_kernel, dim3((n_doms + 63) / 64), dim3(64), 0, s, partials,
-                       n_doms, bpd, out);
+    hipLaunchKernelGGL(mass_final_kernel, dim3(n_doms), dim3(MASS_THREADS), 0, s, partials, bpd, out,
+                       A.flag, flag_out);
     return hipGetLastError();
 }
 
-hipError_t launch_mass(int storage, const void *args, int n_doms, const int *, double *partials,
-                       int bpd, double *out, hipStream_t s) {
+hipError_t launch_mass(int storage, const void *args, int n_doms, double *partials, int bpd, double *out,
+                       int *flag_out, hipStream_t s) {
     switch (storage) {
-        case 0: return mass_t<double>(args, n_doms, partials, bpd, out, s);
-        case 1: return mass_t<float>(args, n_doms, partials, bpd, out, s);
-        case 2: return mass_t<__half>(args, n_doms, partials, bpd, out, s);
-        case 3: return mass_t<C16>(args, n_doms, partials, bpd, out, s);
+        case 0: return mass_t<double>(args, n_doms, partials, bpd, out, flag_out, s);
+        case 1: return mass_t<float>(args, n_doms, partials, bpd, out, flag_out, s);
+        case 2: return mass_t<__half>(args, n_doms, partials, bpd, out, flag_out, s);
+        case 3: return mass_t<C16>(args, n_doms, partials, bpd, out, flag_out, s);
     }
     return hipErrorInvalidValue;
 }
@@ -2389,15 +2401,15 @@ static const StepArgs<T, typename Codec<T>::AT> &args_of(const void *a) {
 
 template <class T>
 static hipError_t velocity_stats_t(const void *args, int n_doms, const void *u, const void *snap,
-                                   double *partials, double *out, hipStream_t s) {
+                                   double *partials, double *out, int *flag_out, hipStream_t s) {
     using AT = typename Codec<T>::AT;
     const auto &A = args_of<T>(args);
     const size_t stride = A.c_plane_bytes / sizeof(AT);
     const AT *ux = static_cast<const AT *>(u), *sx = static_cast<const AT *>(snap);
     hipLaunchKernelGGL(velocity_stats_kernel<AT>, dim3(n_doms * DIAG_BLOCKS), dim3(DIAG_THREADS), 0, s,
                        A.doms, A.mask, ux, ux + stride, sx, sx ? sx + stride : nullptr, partials);
-    hipLaunchKernelGGL(max_final_kernel, dim3((n_doms + 63) / 64), dim3(64), 0, s, partials, n_doms,
-                       out, snap != nullptr);
+    hipLaunchKernelGGL(max_final_kernel, dim3(n_doms), dim3(DIAG_BLOCKS), 0, s, partials, out,
+                       snap != nullptr, A.flag, flag_out);
     return hipGetLastError();
 }
 
@@ -2418,21 +2430,22 @@ static hipError_t region_mass_t(const void *args, int dom, const uint8_t *region
                                 double *out, hipStream_t s) {
     hipLaunchKernelGGL(region_mass_kernel<T>, dim3(DIAG_BLOCKS), dim3(DIAG_THREADS), 0, s, args_of<T>(args),
                        dom, region, partials);
-    hipLaunchKernelGGL(sum4_final_kernel, dim3(1), dim3(64), 0, s, partials, out);
+    hipLaunchKernelGGL(sum4_final_kernel, dim3(1), dim3(DIAG_BLOCKS), 0, s, partials, out);
     return hipGetLastError();
 }
 
 template <class T>
-static hipError_t crossings_t(const void *args, int dom, const int *rows, int n_rows, double *out,
+static hipError_t crossings_t(const void *args, int dom, int nx, const int *rows, int n_rows, double *out,
                               hipStream_t s) {
-    hipLaunchKernelGGL(crossing_kernel<T>, dim3(n_rows), dim3(DIAG_THREADS), 0, s, args_of<T>(args), dom,
-                       rows, out);
+    const int threads = nx <= 64 ? 64 : (nx <= 256 ? 256 : CROSS_THREADS);
+    hipLaunchKernelGGL(crossing_kernel<T>, dim3(n_rows), dim3(threads), 0, s, args_of<T>(args), dom, rows,
+                       out);
     return hipGetLastError();
 }
 
 hipError_t launch_velocity_stats(int storage, const void *args, int n_doms, const void *u,
-                                 const void *snap, double *partials, double *out, hipStream_t s) {
-#define CALL(T) velocity_stats_t<T>(args, n_doms, u, snap, partials, out, s)
+                                 const void *snap, double *partials, double *out, int *flag_out, hipStream_t s) {
+#define CALL(T) velocity_stats_t<T>(args, n_doms, u, snap, partials, out, flag_out, s)
     switch (storage) {
         case 0: return CALL(double);
         case 1: return CALL(float);
@@ -2469,9 +2482,9 @@ hipError_t launch_region_mass(int storage, const void *args, int dom, const uint
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_crossings(int storage, const void *args, int dom, const int *rows, int n_rows,
+hipError_t launch_crossings(int storage, const void *args, int dom, int nx, const int *rows, int n_rows,
                             double *out, hipStream_t s) {
-#define CALL(T) crossings_t<T>(args, dom, rows, n_rows, out, s)
+#define CALL(T) crossings_t<T>(args, dom, nx, rows, n_rows, out, s)
     switch (storage) {
         case 0: return CALL(double);
         case 1: return CALL(float);
@@ -2511,11 +2524,11 @@ hipError_t noalloc_scratch(int device, void **out) {
     return hipSuccess;
 }
 
-hipError_t launch_crossings_noalloc(int storage, const void *args, int dom, void *scratch_dev,
+hipError_t launch_crossings_noalloc(int storage, const void *args, int dom, int nx, void *scratch_dev,
                                     int n_rows, hipStream_t s) {
     const int *rows = static_cast<const int *>(scratch_dev);
     double *out = reinterpret_cast<double *>(static_cast<char *>(scratch_dev) + NOALLOC_OUT_OFFSET);
-    return launch_crossings(storage, args, dom, rows, n_rows, out, s);
+    return launch_crossings(storage, args, dom, nx, rows, n_rows, out, s);
 }
 
 }  // namespace lbmcg
