@@ -48,24 +48,33 @@ __device__ __forceinline__ AT wgt(int a) {
     return a == 0 ? AT(4.0 / 9.0) : (a < 5 ? AT(1.0 / 9.0) : AT(1.0 / 36.0));
 }
 
-// Reciprocal and square root: IEEE in FP64 (the FP64 path is checked element by element
-// against a plain FP64 evaluation); the hardware's 1-ulp instructions in FP32.
-__device__ __forceinline__ double rcp(double x) { return 1.0 / x; }
+// Reciprocal of a density, a viscosity or a weight sum (positive, of order one).  FP64: the
+// hardware's estimate with two Newton steps, within one ulp, in 5 instructions where the IEEE
+// division takes 12 to also cover operands near the ends of the exponent range; FP32: the
+// hardware's 1-ulp instruction.
+__device__ __forceinline__ double rcp(double x) {
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(fma(-x, r, 1.0), r, r);
+    return fma(fma(-x, r, 1.0), r, r);
+}
 __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ __forceinline__ double fsqrt(double x) { return sqrt(x); }
 __device__ __forceinline__ float fsqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
 
-// a / b: IEEE in FP64; in FP32 the 1-ulp reciprocal ib refined by one Newton step, which removes
-// the reciprocal's systematic bias (the red fraction c = rho_R / rho must not drift the
-// colour masses).
-__device__ __forceinline__ double quotient(double a, double b, double) { return a / b; }
-__device__ __forceinline__ float quotient(float a, float b, float ib) {
-    const float q = a * ib;
-    return fmaf(ib, fmaf(-q, b, a), q);
+// a / b with ib = rcp(b), corrected by the residual: exactly 1 for a = b and free of the
+// reciprocal's systematic bias (the red fraction c = rho_R / rho must not drift the colour
+// masses); in FP64 the correctly rounded quotient but for rare last-bit cases.
+template <class AT>
+__device__ __forceinline__ AT quotient(AT a, AT b, AT ib) {
+    const AT q = a * ib;
+    return fma(ib, fma(-q, b, a), q);
 }
 
 // Colour indicator (Eq. 12), exactly +-1 in pure phases.
-__device__ __forceinline__ double colour_indicator(double rR, double rB) { return (rR - rB) / (rR + rB); }
+__device__ __forceinline__ double colour_indicator(double rR, double rB) {
+    const double s = rR + rB;
+    return quotient(rR - rB, s, rcp(s));
+}
 __device__ __forceinline__ float colour_indicator(float rR, float rB) {
     return rB == 0.0f ? 1.0f : (rR == 0.0f ? -1.0f : (rR - rB) * rcp(rR + rB));
 }
@@ -80,9 +89,12 @@ __device__ __forceinline__ float colour_indicator(float rR, float rB) {
 __device__ __forceinline__ void unit_normal(double gx, double gy, double eps, double &g, double &nx,
                                             double &ny) {
 #pragma clang fp contract(on)
-    g = sqrt(gx * gx + gy * gy);
-    nx = g > eps ? gx / g : 0.0;
-    ny = g > eps ? gy / g : 0.0;
+    const double g2 = gx * gx + gy * gy;
+    g = sqrt(g2);
+    const bool on = g > eps;
+    const double ig = rcp(g);
+    nx = on ? gx * ig : 0.0;
+    ny = on ? gy * ig : 0.0;
 }
 __device__ __forceinline__ void unit_normal(float gx, float gy, float eps, float &g, float &nx,
                                             float &ny) {
