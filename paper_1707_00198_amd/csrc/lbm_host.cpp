@@ -416,7 +416,9 @@ std::vector<WorkItem> build_items(const std::vector<lbm_domain_desc> &d, const T
 // 16 or 12 rows as long as they give 512 items (two blocks per CU): batches of 60-row channels
 // (15 or 44 of 630 x 60) ran 15-23 % faster in 16-row chunks than in 8-row ones, whose halo
 // rows double the work, while a single 2000 x 100 channel (266 items at 16 rows) ran fastest
-// in 8-row chunks, where more items outweigh the halo.
+// in 8-row chunks, where more items outweigh the halo.  FP64 marches fewer blocks at a time and
+// takes 32 rows from 2400 items on: 24 cylinder boxes 400 x 400 201 us against 220 in 16-row
+// chunks, 16384 x 256 249 against 254, 30 channels of the sweep 396 against 417.
 int auto_chunk(const std::vector<lbm_domain_desc> &d, TileShape t, int storage) {
     const auto items = [&](int ch) {
         t.chunk = ch;
@@ -424,6 +426,7 @@ int auto_chunk(const std::vector<lbm_domain_desc> &d, TileShape t, int storage) 
     };
     for (int ch : {64, 48, 32, 24})
         if (items(ch) >= 4096) return ch;
+    if (storage == 0 && items(32) >= 2400) return 32;
     for (int ch : {16, 12})
         if (items(ch) >= 512) return ch;
     return 8;
@@ -439,14 +442,14 @@ constexpr int DEFAULT_COLS = 1;
 // The built-in shape of a batch: the patch kernel, which takes a work item at once, while its
 // repeated halo rows cost less than the march's iterations (us per step on an MI355X, patch
 // against the best march):
-//  FP32 arithmetic, binary16 / FP32 storage: items of 8 rows up to 1536 of them (234 items 8.3
-//    against 20, 1404 items 20.4 against 33; 1600 items 24 where items of 24 rows take 20), then
-//    items of 24 rows: 44 channels 630 x 60 42 / 45 against 63, 16384 x 512 177 / 218 against
-//    186 / 250, 60 channels of the sweep (12240 items) 321 / 369 against 325 / 406.  In the
-//    16-bit storages only up to 16384 items: the gain is gone there; FP32 is bound by HBM.
-//  FP64: items of 8 rows up to 10240 (234 items 10.6 against 21.7, 4224 items 113 against 119,
-//    9669 items 242 against 248; 19338 items 441 against 411).
-constexpr size_t PATCH_ITEMS = 1536, PATCH_TALL_ITEMS_16 = 16384, PATCH_ITEMS_F64 = 10240;
+//  FP32 arithmetic, binary16 / FP32 storage: items of 8 rows up to 1408 of them (234 items 8.2
+//    against 20, 1404 items 20.4 against 33; 1600 items 23.4 where items of 24 rows take 19.9),
+//    then items of 24 rows: 44 channels 630 x 60 42 / 45 against 63, 16384 x 512 176 / 218 against
+//    186 / 250, 60 channels of the sweep (12240 items) 320 / 369 against 320 / 406.  In the 16-bit
+//    storages only up to 16384 items: the gain is gone there; FP32 is bound by HBM.
+//  FP64: items of 8 rows up to 8192 (234 items 10.3 against 21.7, 4224 items 106 against 118,
+//    4800 items 122 against 123; 9600 items, 24 cylinder boxes, 226 against 201).
+constexpr size_t PATCH_ITEMS = 1408, PATCH_TALL_ITEMS_16 = 16384, PATCH_ITEMS_F64 = 8192;
 TileShape builtin_tile(const std::vector<lbm_domain_desc> &d, int storage) {
     const TileShape patch{PATCH_ROWS, 8, 1, 1}, tall{PATCH_TALL_ROWS, 8, 1, 1};
     if (build_items(d, patch, storage).size() <= (storage == 0 ? PATCH_ITEMS_F64 : PATCH_ITEMS)) return patch;

@@ -30,7 +30,7 @@ inline int halo_x(int storage) { return storage == 0 ? HALO_X64 : HALO_X32; }
 // Work items of 8 rows and, with FP32 arithmetic, of 24 rows on blocks of 8 run on the patch
 // kernel, which holds a whole item with its halo and takes the colour state around it from extra
 // LDS rows and columns in every storage.
-constexpr int PATCH_ROWS = 8, PATCH_TALL_ROWS = 24, PATCH_HALO = 4;
+constexpr int PATCH_ROWS = 8, PATCH_TALL_ROWS = 24, PATCH_HALO = 4, PATCH_WAVES = 16;
 struct TileShape {
     int chunk, waves, cols, npl;
     bool patch(bool f64) const {

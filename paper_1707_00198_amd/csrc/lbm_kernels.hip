@@ -395,17 +395,22 @@ __device__ __forceinline__ bool pull_outside(const Nbr &n, int a) {
     return (n.lo && EX[a] == 1) || (n.hi && EX[a] == -1);
 }
 
-// Adds the population f that direction a pulls from a node of colour state (c, v) to the red
-// density (c f + w_a e_a . v, Eq. 14) and to the total.  The total takes the same steps as the
-// red density, so where every source is pure red (c = 1, v = 0) the two stay equal.  The sums
-// run from the smallest populations to the largest (diagonal, axis, rest): the partial sums, and
-// with them the rounding errors of the colour split, then stay small for longest.
+// e_a . v of a colour state; opposite directions give exactly opposite values.
 template <class AT>
-__device__ __forceinline__ void add_pull(int a, AT f, AT c, AT vx, AT vy, AT &rR, AT &tot) {
+__device__ __forceinline__ AT along(int a, AT vx, AT vy) {
+    return EX[a] == 0 ? (EY[a] > 0 ? vy : -vy)
+                      : (EY[a] == 0 ? (EX[a] > 0 ? vx : -vx)
+                                    : (EX[a] > 0 ? vx : -vx) + (EY[a] > 0 ? vy : -vy));
+}
+
+// Adds the population f that direction a pulls from a node of colour state (c, v) to the red
+// density (c f + w_a e_a . v, Eq. 14; ev = e_a . v) and to the total.  The total takes the same
+// steps as the red density, so where every source is pure red (c = 1, v = 0) the two stay equal.
+// The sums run from the smallest populations to the largest (diagonal, axis, rest): the partial
+// sums, and with them the rounding errors of the colour split, then stay small for longest.
+template <class AT>
+__device__ __forceinline__ void add_pull(int a, AT f, AT c, AT ev, AT &rR, AT &tot) {
 #pragma clang fp contract(on)
-    const AT ev = EX[a] == 0 ? (EY[a] > 0 ? vy : -vy)
-                             : (EY[a] == 0 ? (EX[a] > 0 ? vx : -vx)
-                                           : (EX[a] > 0 ? vx : -vx) + (EY[a] > 0 ? vy : -vy));
     const AT p = wgt<AT>(a) * ev;
     const AT r = c * f + p;
     rR = rR + r;
@@ -415,19 +420,18 @@ __device__ constexpr int PULL_ORDER[8] = {5, 6, 7, 8, 1, 2, 3, 4};
 
 // Densities of a node that pulls every population from a fluid neighbour.
 template <class AT, class ColourFn>
-__device__ __forceinline__ void gather_interior(ParC<AT> &P, const AT d[9], AT &rR, AT &rB, ColourFn colour) {
+__device__ __forceinline__ void gather_interior(ParC<AT> &P, const AT d[9], AT cself, AT &rR, AT &rB, ColourFn colour) {
 #pragma clang fp contract(on)
-    AT tot = AT(0), c, vx, vy;
+    AT tot = AT(0), c, ev;
     rR = AT(0);
 #pragma unroll
     for (int k = 0; k < 8; k++) {
         const int a = PULL_ORDER[k];
-        colour(a, c, vx, vy);
-        add_pull(a, (a < 5 ? P.w_axis : P.w_diag) + d[a], c, vx, vy, rR, tot);
+        colour(a, false, c, ev);
+        add_pull(a, (a < 5 ? P.w_axis : P.w_diag) + d[a], c, ev, rR, tot);
     }
-    colour(0, c, vx, vy);
     const AT f0 = P.w_rest + d[0];
-    const AT r0 = c * f0;
+    const AT r0 = cself * f0;
     rR = rR + r0;
     tot = tot + f0;
     rB = tot - rR;
@@ -436,20 +440,20 @@ __device__ __forceinline__ void gather_interior(ParC<AT> &P, const AT d[9], AT &
 // Completes the post-streaming populations d[] of fluid node (x, y) whose interior pulls are
 // already in d[] (and whose own-node snapshot values are in d[] in snapshot mode): half-way
 // bounce-back on links from solid nodes, Zou-He inlet and convective outlet unknowns; and
-// returns the red and blue densities of Eq. 16.  colour(a, c, vx, vy) yields the colour state
-// of the pull source of direction a (a = 0: the node itself).
+// returns the red and blue densities of Eq. 16.  colour(a, bounced, c, ev) yields the red fraction c
+// and e_a . v that direction a >= 1 pulls: its source's, or (bounced) the node's own, reversed;
+// own() yields the node's red fraction.
 // BOUNCED: d[] already holds the bounced populations f_opp(a) of the node itself for pulls from
 // solid nodes (the step kernel's prefetch redirects those loads).
-template <bool BOUNCED, class T, class AT, class ColourFn>
+template <bool BOUNCED, class T, class AT, class ColourFn, class OwnFn>
 __device__ __forceinline__ void finish_gather(const StepArgs<T, AT> &A, DomC &D, int x, int y,
                                               uint32_t m, const Nbr &nb, bool write_hist, AT d[9],
-                                              AT &rR, AT &rB, ColourFn colour) {
+                                              AT &rR, AT &rB, ColourFn colour, OwnFn own) {
 #pragma clang fp contract(on)
     const size_t self = nb.row[1] + x;
     ParC<AT> &P = par(D, AT());
     const AT rho0 = P.rho0;
-    AT cself, vxs, vys;
-    colour(0, cself, vxs, vys);
+    const AT cself = own();
     rR = AT(0);
     rB = AT(0);
     const AT wr[3] = {P.w_rest, P.w_axis, P.w_diag};
@@ -462,7 +466,7 @@ __device__ __forceinline__ void finish_gather(const StepArgs<T, AT> &A, DomC &D,
         rB = tot - rR;
     } else if ((m & 0xFFu) == 0u && !nb.lo && !nb.hi) {
         // interior node: every population is pulled from a fluid neighbour
-        gather_interior(P, d, rR, rB, colour);
+        gather_interior(P, d, cself, rR, rB, colour);
     } else {
         if (!BOUNCED) {
 #pragma unroll
@@ -508,14 +512,12 @@ __device__ __forceinline__ void finish_gather(const StepArgs<T, AT> &A, DomC &D,
         for (int k = 0; k < 8; k++) {
             const int a = PULL_ORDER[k];
             const bool outside = pull_outside(nb, a), bounced = (m & (1u << (OPP[a] - 1))) != 0;
-            AT c, vx, vy;
-            colour(a, c, vx, vy);
-            // from a solid node: the node's own colour state, reversed; across the inlet: pure
-            // red; across the outlet: the node's red fraction
-            c = outside ? (EX[a] > 0 ? AT(1) : cself) : (bounced ? cself : c);
-            vx = outside ? AT(0) : (bounced ? -vxs : vx);
-            vy = outside ? AT(0) : (bounced ? -vys : vy);
-            add_pull(a, wr[a < 5 ? 1 : 2] + d[a], c, vx, vy, rR, tot);
+            AT c, ev;
+            colour(a, bounced, c, ev);
+            // across the inlet: pure red; across the outlet: the node's red fraction
+            c = outside ? (EX[a] > 0 ? AT(1) : cself) : c;
+            ev = outside ? AT(0) : ev;
+            add_pull(a, wr[a < 5 ? 1 : 2] + d[a], c, ev, rR, tot);
         }
         const AT f0 = wr[0] + d[0];
         const AT r0 = cself * f0;
@@ -531,7 +533,21 @@ __device__ __forceinline__ void finish_gather(const StepArgs<T, AT> &A, DomC &D,
     }
 }
 
-// Gather with colour state from global memory (read-back and reductions).
+// finish_gather() with the colour state from global memory (read-back and reductions).
+template <class T, class AT>
+__device__ __forceinline__ void gather_from_memory(const StepArgs<T, AT> &A, DomC &D, int x, int y, uint32_t m,
+                                                   const Nbr &nb, AT d[9], AT &rR, AT &rB) {
+    finish_gather<false>(
+        A, D, x, y, m, nb, false, d, rR, rB,
+        [&](int a, bool bounced, AT &c, AT &ev) {
+            const size_t src = bounced ? nb.row[1] + x : pull_src(nb, a);
+            c = A.cin[src];
+            ev = along(a, A.vxin[src], A.vyin[src]);
+            ev = bounced ? -ev : ev;
+        },
+        [&]() { return A.cin[nb.row[1] + x]; });
+}
+
 template <class T, class AT>
 __device__ __forceinline__ void gather_global(const StepArgs<T, AT> &A, DomC &D, int x, int y,
                                               uint32_t m, AT d[9], AT &rR, AT &rB) {
@@ -542,12 +558,7 @@ __device__ __forceinline__ void gather_global(const StepArgs<T, AT> &A, DomC &D,
         const size_t src = A.own ? self : pull_src(nb, a);
         d[a] = Codec<T>::load(A.fin + a * A.plane + src, a);
     }
-    finish_gather<false>(A, D, x, y, m, nb, false, d, rR, rB, [&](int a, AT &c, AT &vx, AT &vy) {
-        const size_t src = (a == 0 || A.own) ? self : pull_src(nb, a);
-        c = A.cin[src];
-        vx = A.own ? AT(0) : A.vxin[src];
-        vy = A.own ? AT(0) : A.vyin[src];
-    });
+    gather_from_memory(A, D, x, y, m, nb, d, rR, rB);
 }
 
 // Contact-angle correction of the colour gradient on an outermost fluid node (Eqs. 30-36):
@@ -790,7 +801,6 @@ __global__ __launch_bounds__(TILE_LANES *R *C, sizeof(typename Codec<T>::AT) == 
     const int xe = D.open_x ? min(max(X, 0), D.nx - 1) : wrap(X, D.nx);
     const bool edge_item = D.open_x && (base < 0 || base + TL > D.nx);
     const int edge_lane = xe != X && D.open_x ? xe - base : -1;
-    const int lanes_of[3] = {lane - 1, lane, lane + 1};
     const bool out_lane = lane >= HX && lane < TL - HX && X < D.nx;
     const bool gather_lane = GO || (lane >= 1 && lane < TL - 1);
     // node column of the ghost colour-state column a lane loads (lane 0: left, lane 1: right)
@@ -977,14 +987,15 @@ __global__ __launch_bounds__(TILE_LANES *R *C, sizeof(typename Codec<T>::AT) == 
         if (gather_lane && !(m & SELF_SOLID)) {
             const int yw = wrap(ya, D.ny);
             const Nbr nb = make_nbr(D, xe, yw);
+            const AT own_c = s_c[sl][lane + GO], own_vx = s_vx[sl][lane + GO], own_vy = s_vy[sl][lane + GO];
             finish_gather<true>(A, D, xe, yw, m, nb, !A.diag, dn, rRn, rBn,
-                                [&](int a, AT &c, AT &vx, AT &vy) {
-                                    const int s2 = (ya - EY[a]) & (Q - 1);
-                                    const int l2 = lanes_of[1 - EX[a]] + GO;
-                                    c = s_c[s2][l2];
-                                    vx = s_vx[s2][l2];
-                                    vy = s_vy[s2][l2];
-                                });
+                                [&](int a, bool bounced, AT &c, AT &ev) {
+                                    const int s2 = (ya - EY[a]) & (Q - 1), l2 = lane - EX[a] + GO;
+                                    const AT cs = s_c[s2][l2], vx = s_vx[s2][l2], vy = s_vy[s2][l2];
+                                    c = bounced ? own_c : cs;
+                                    ev = bounced ? along(OPP[a], own_vx, own_vy) : along(a, vx, vy);
+                                },
+                                [&]() { return own_c; });
             rn = colour_indicator(rRn, rBn);
             rNn = rn;
         }
@@ -1178,18 +1189,20 @@ __global__ __launch_bounds__(TILE_LANES *R *C, sizeof(typename Codec<T>::AT) == 
 // class word; a wavefront whose rows touch a wall then loads the bounced ones.  Node arithmetic
 // and results are step_kernel's, bit for bit.
 //
-// 16 wavefronts of one row (8 output rows): the shortest time of one block, for small lattices.
-// With FP32 arithmetic 16 of two rows (24 output rows of 32), held to 64 registers so that two
-// blocks share a CU, one loading while the other computes; with FP64 arithmetic, where two rows
-// need 118 registers, two blocks of 8 wavefronts of two rows do the same for 8 output rows.
-template <class T, int NW, int K, bool WV>
-__global__ __launch_bounds__(TILE_LANES *NW, sizeof(typename Codec<T>::AT) == 4 ? 8 : 4) void patch_kernel(const StepArgs<T, typename Codec<T>::AT> A) {
+// One row per wavefront (8 output rows) gives the shortest time of one block, for small lattices;
+// two rows (24 output rows of 32; FP32 arithmetic) repeat fewer halo rows.  OCC = 8 wavefronts per
+// SIMD holds the kernel to 64 vector and 78 scalar registers, so that two blocks share a CU, one
+// loading while the other computes (44 channels of 630 x 60 in binary16: 45 us a step against 54).
+template <class T, int K, int OCC, bool WV>
+__global__ __launch_bounds__(TILE_LANES *PATCH_WAVES, OCC) void patch_kernel(const StepArgs<T, typename Codec<T>::AT> A) {
     using AT = typename Codec<T>::AT;
-    constexpr int TX = TILE_LANES, TY = NW * K, H = PATCH_HALO;
+    constexpr int TX = TILE_LANES, TY = PATCH_WAVES * K, H = PATCH_HALO;
     constexpr int CW = TX + 2, CH = TY + 2;  // colour state: one more column and row per side
     constexpr uint32_t SB = sizeof(T), CB = sizeof(AT);
-    __shared__ AT s_c[CH * CW], s_vx[CH * CW], s_vy[CH * CW], s_rn[TY * TX];
-    __shared__ int s_wall[NW];
+    // colour state c, v_x, v_y and v_x + v_y, v_y - v_x: a diagonal pull then reads one value of v
+    // instead of two (with FP64 arithmetic stage A is as long as its LDS reads)
+    __shared__ AT s_c[CH * CW], s_vx[CH * CW], s_vy[CH * CW], s_vs[CH * CW], s_vd[CH * CW], s_rn[TY * TX];
+    __shared__ int s_wall[PATCH_WAVES];
     // normals take the place of v, which is dead after stage A
     AT *const s_nx = s_vx, *const s_ny = s_vy;
 
@@ -1238,7 +1251,7 @@ __global__ __launch_bounds__(TILE_LANES *NW, sizeof(typename Codec<T>::AT) == 4 
         AT c0[K], vx0[K], vy0[K];
         // the ring of colour state around the tile: rows -1 and TY, then columns -1 and TX
         constexpr int RING = 2 * CW + 2 * TY;
-        static_assert(RING <= TX * NW, "one ring node per thread");
+        static_assert(RING <= TX * PATCH_WAVES, "one ring node per thread");
         const int t = threadIdx.x;
         const int rk = t - 2 * CW;
         const int ry = t < 2 * CW ? (t < CW ? -1 : TY) : rk % TY;
@@ -1285,6 +1298,8 @@ __global__ __launch_bounds__(TILE_LANES *NW, sizeof(typename Codec<T>::AT) == 4 
                 s_c[kc] = c0[k];
                 s_vx[kc] = vx0[k];
                 s_vy[kc] = vy0[k];
+                s_vs[kc] = vx0[k] + vy0[k];
+                s_vd[kc] = vy0[k] - vx0[k];
             }
         }
         if (t < RING) {
@@ -1292,6 +1307,8 @@ __global__ __launch_bounds__(TILE_LANES *NW, sizeof(typename Codec<T>::AT) == 4 
             s_c[k] = c1;
             s_vx[k] = vx1;
             s_vy[k] = vy1;
+            s_vs[k] = vx1 + vy1;
+            s_vd[k] = vy1 - vx1;
         }
     }
     // bounced populations and wall normals, where a row has any
@@ -1336,13 +1353,10 @@ __global__ __launch_bounds__(TILE_LANES *NW, sizeof(typename Codec<T>::AT) == 4 
             for (int a = 0; a < 9; a++) d[k][a] = Codec<T>::decode(f[k][a], a);
             rR[k] = rB[k] = AT(0);
         }
-        const auto colour_at = [&](int k) {
-            return [&, k](int a, AT &c, AT &vx, AT &vy) {
-                const int q = kc0 + (k - EY[a]) * CW - EX[a];
-                c = s_c[q];
-                vx = s_vx[q];
-                vy = s_vy[q];
-            };
+        const auto ev_at = [&](int a, int q) {
+            if (a < 5) return along(a, s_vx[q], s_vy[q]);
+            const AT v = EX[a] == EY[a] ? s_vs[q] : s_vd[q];
+            return EY[a] > 0 ? v : -v;
         };
         if (need) {
 #pragma unroll
@@ -1351,7 +1365,23 @@ __global__ __launch_bounds__(TILE_LANES *NW, sizeof(typename Codec<T>::AT) == 4 
                 if (!beyond && !(m[k] & SELF_SOLID)) {
                     const int yw = wrap(ya + k, ny_);
                     const Nbr nb = make_nbr(D, xe, yw);
-                    finish_gather<true>(A, D, xe, yw, m[k], nb, !A.diag, d[k], rR[k], rB[k], colour_at(k));
+                    const int kc = kc0 + k * CW;
+                    const AT own_c = s_c[kc], own_vx = s_vx[kc], own_vy = s_vy[kc];
+                    finish_gather<true>(
+                        A, D, xe, yw, m[k], nb, !A.diag, d[k], rR[k], rB[k],
+                        [&](int a, bool bounced, AT &c, AT &ev) {
+                            const int src = kc - EY[a] * CW - EX[a];
+                            if (sizeof(AT) == 8) {  // choosing the address saves registers
+                                const int q = bounced ? kc : src;
+                                c = s_c[q];
+                                ev = bounced ? -ev_at(a, q) : ev_at(a, q);
+                            } else {
+                                const AT cs = s_c[src], es = ev_at(a, src);
+                                c = bounced ? own_c : cs;
+                                ev = bounced ? along(OPP[a], own_vx, own_vy) : es;
+                            }
+                        },
+                        [&]() { return own_c; });
                     rn = colour_indicator(rR[k], rB[k]);
                 }
                 if (edge_item) rn = __shfl(rn, edge_lane);
@@ -1361,7 +1391,7 @@ __global__ __launch_bounds__(TILE_LANES *NW, sizeof(typename Codec<T>::AT) == 4 
     }
     if (lane == 0) s_wall[w] = wall;
     __syncthreads();
-    const bool any_wall = __builtin_amdgcn_ballot_w64(lane < NW && s_wall[lane % NW] != 0) != 0;
+    const bool any_wall = __builtin_amdgcn_ballot_w64(lane < PATCH_WAVES && s_wall[lane % PATCH_WAVES] != 0) != 0;
 
     // ---- B: virtual colour indicator on outermost solid nodes (Eq. 29)
     if (any_wall) {
@@ -1809,14 +1839,15 @@ __global__ __launch_bounds__(TILE_LANES *R, 2) void pair_kernel(const StepArgs<T
             if (gath[k] && !(ms[k] & SELF_SOLID)) {
                 const Nbr nb = make_nbr(D, xe[k], yw);
                 const int ck = col[k];
+                const AT own_c = s_c[sl][ck], own_vx = s_vx[sl][ck], own_vy = s_vy[sl][ck];
                 finish_gather<true>(A, D, xe[k], yw, ms[k], nb, !A.diag, dn[k], rRn[k], rBn[k],
-                                    [&](int a, AT &c, AT &vx, AT &vy) {
-                                        const int s2 = (ya - EY[a]) & (Q - 1);
-                                        const int l2 = ck - EX[a];
-                                        c = s_c[s2][l2];
-                                        vx = s_vx[s2][l2];
-                                        vy = s_vy[s2][l2];
-                                    });
+                                    [&](int a, bool bounced, AT &c, AT &ev) {
+                                        const int s2 = (ya - EY[a]) & (Q - 1), l2 = ck - EX[a];
+                                        const AT cs = s_c[s2][l2], vx = s_vx[s2][l2], vy = s_vy[s2][l2];
+                                        c = bounced ? own_c : cs;
+                                        ev = bounced ? along(OPP[a], own_vx, own_vy) : along(a, vx, vy);
+                                    },
+                                    [&]() { return own_c; });
                 rn[k] = colour_indicator(rRn[k], rBn[k]);
                 rNn[k] = rn[k];
             }
@@ -2049,12 +2080,7 @@ __global__ void read_kernel(const StepArgs<T, typename Codec<T>::AT> A, int dom,
             for (int a = 0; a < 9; a++)
                 d[a] = Codec<T>::load(A.fin + a * A.plane + (A.own ? self : pull_src(nb, a)),
                                       a);
-            finish_gather<false>(A, D, x, y, m, nb, false, d, rR, rB, [&](int a, AT &c, AT &vx, AT &vy) {
-                const size_t src = (a == 0 || A.own) ? self : pull_src(nb, a);
-                c = A.cin[src];
-                vx = A.own ? AT(0) : A.vxin[src];
-                vy = A.own ? AT(0) : A.vyin[src];
-            });
+            gather_from_memory(A, D, x, y, m, nb, d, rR, rB);
             const AT cself = A.cin[self];
             const AT vxs = A.own ? AT(0) : A.vxin[self], vys = A.own ? AT(0) : A.vyin[self];
 #pragma unroll
@@ -2312,7 +2338,10 @@ __global__ __launch_bounds__(CROSS_THREADS) void crossing_kernel(
 }
 
 // ------------------------------------------------------------------- launchers
-constexpr int PATCH64_SINGLE_ROW_ITEMS = 512;
+// FP64 patches at 64 registers, two blocks on a CU, once there are more blocks than CUs; up to that
+// their few spilled registers only cost (200 x 100 droplet 8.04 against 8.34 us a step, 52 items;
+// 2000 x 100 channel, 468 items, 16.5 against 15.7, 44 channels, 4224 items, 123 against 110).
+constexpr int PATCH64_ROOMY_ITEMS = 256;
 template <class T, bool WV>
 static hipError_t step_t(const void *args, int n_items, const TileShape &t, hipStream_t s) {
     const auto &A = *static_cast<const StepArgs<T, typename Codec<T>::AT> *>(args);
@@ -2328,14 +2357,13 @@ static hipError_t step_t(const void *args, int n_items, const TileShape &t, hipS
     if (t.npl != 1) return hipErrorInvalidValue;
     constexpr bool f64 = sizeof(typename Codec<T>::AT) == 8;
     if (t.patch(f64)) {
-        // FP64: 16 wavefronts of one row while there are at most two blocks for each of the 256 CUs
-        // (234 items 10.6 us a step), then 8 of two rows (4224 items 113 us, and 127 with the other)
-        if (f64 && n_items > PATCH64_SINGLE_ROW_ITEMS)
-            hipLaunchKernelGGL((patch_kernel<T, 8, 2, WV>), dim3(n_items), dim3(TILE_LANES * 8), 0, s, A);
+        const dim3 grid(n_items), block(TILE_LANES * PATCH_WAVES);
+        if (f64 && n_items <= PATCH64_ROOMY_ITEMS)
+            hipLaunchKernelGGL((patch_kernel<T, 1, f64 ? 4 : 8, WV>), grid, block, 0, s, A);
         else if (f64 || t.chunk == PATCH_ROWS)
-            hipLaunchKernelGGL((patch_kernel<T, 16, 1, WV>), dim3(n_items), dim3(TILE_LANES * 16), 0, s, A);
+            hipLaunchKernelGGL((patch_kernel<T, 1, 8, WV>), grid, block, 0, s, A);
         else
-            hipLaunchKernelGGL((patch_kernel<T, f64 ? 8 : 16, 2, WV>), dim3(n_items), dim3(TILE_LANES * (f64 ? 8 : 16)), 0, s, A);
+            hipLaunchKernelGGL((patch_kernel<T, f64 ? 1 : 2, 8, WV>), grid, block, 0, s, A);
     }
     else if (t.cols == 2)
         hipLaunchKernelGGL((step_kernel<T, 4, 2, WV>), dim3(n_items), dim3(TILE_LANES * 8), 0, s, A);
