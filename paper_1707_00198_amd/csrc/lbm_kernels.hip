@@ -14,8 +14,9 @@
 // The step kernel marches a 64-column window up a chunk of rows: 56 output columns and a
 // 4-column halo on each side (the dependency radius next to walls), with the colour state of
 // the column beyond each halo in two extra LDS columns; with FP64 arithmetic, 54 output columns
-// and a 5-column halo whose outermost lanes hold that colour state.  Every iteration advances R rows (4 by default) through five stages kept
-// in LDS ring buffers, each lagging the previous one by a row:
+// and a 5-column halo whose outermost lanes hold that colour state.  Every iteration advances
+// R rows (4 by default) through five stages kept in LDS ring buffers, each lagging the previous
+// one by a row:
 //   A  pull the 9 populations (bounce-back, inlet and outlet completion), rho_R, rho_B, rho^N
 //   B  virtual rho^N on outermost solid nodes (Eq. 29)
 //   C  colour gradient (Eq. 28), wetting correction on outermost fluid nodes (Eqs. 30-36),
@@ -27,8 +28,12 @@
 // earlier, so the populations stay in registers: each population is read once from HBM and
 // written once per step (halo columns are re-read by the neighbouring window, from cache).
 // Per-domain wetting variants of Sec. III A (scheme (b), Eq. 48; the surface-energy rule)
-// change stages B-E.  A diagnostic launch runs the same kernel without writing the state and
-// outputs the velocity of Eq. 17 and, optionally, the contact-line nodes instead.
+// change stages B-E.
+//
+// Batches of few work items take a second form of the same step, patch_kernel: a short work item
+// held whole by a block of 16 wavefronts, each stage once.  All one-column forms share the node
+// arithmetic and give the same bits.  A diagnostic launch runs the same kernel without writing
+// the state and outputs the velocity of Eq. 17 and, optionally, the contact-line nodes instead.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
@@ -682,6 +687,10 @@ __device__ __forceinline__ Rsrc make_rsrc(const void *base, uint32_t bytes) {
                                              0x00020000);
 }
 
+// Cache policy of a store (the instruction's cache bits): left dirty in the XCD's L2, written
+// through it, or streamed past it.  The march always takes the first: rows then complete each
+// other's partial lines in the L2.
+constexpr int WRITE_BACK = 0, WRITE_THROUGH = 16, WRITE_STREAM = 2;
 template <class V>
 struct Buf;
 template <>
@@ -689,9 +698,10 @@ struct Buf<double> {
     __device__ static double load(Rsrc r, uint32_t vo, uint32_t so) {
         return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, vo, so, 0));
     }
+    template <int POLICY = WRITE_BACK>
     __device__ static void store(Rsrc r, uint32_t vo, uint32_t so, double v) {
         using B = decltype(__builtin_amdgcn_raw_buffer_load_b64(r, 0, 0, 0));
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(B, v), r, vo, so, 0);
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(B, v), r, vo, so, POLICY);
     }
 };
 template <>
@@ -699,8 +709,9 @@ struct Buf<float> {
     __device__ static float load(Rsrc r, uint32_t vo, uint32_t so) {
         return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, vo, so, 0));
     }
+    template <int POLICY = WRITE_BACK>
     __device__ static void store(Rsrc r, uint32_t vo, uint32_t so, float v) {
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, vo, so, 0);
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, vo, so, POLICY);
     }
 };
 // Two consecutive values (the interleaved wall normal of a node) in one load.
@@ -722,8 +733,9 @@ struct Buf<__half> {
     __device__ static __half load(Rsrc r, uint32_t vo, uint32_t so) {
         return __builtin_bit_cast(__half, __builtin_amdgcn_raw_buffer_load_b16(r, vo, so, 0));
     }
+    template <int POLICY = WRITE_BACK>
     __device__ static void store(Rsrc r, uint32_t vo, uint32_t so, __half v) {
-        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, v), r, vo, so, 0);
+        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, v), r, vo, so, POLICY);
     }
 };
 template <>
@@ -731,13 +743,15 @@ struct Buf<C16> {
     __device__ static C16 load(Rsrc r, uint32_t vo, uint32_t so) {
         return C16{__builtin_amdgcn_raw_buffer_load_b16(r, vo, so, 0)};
     }
+    template <int POLICY = WRITE_BACK>
     __device__ static void store(Rsrc r, uint32_t vo, uint32_t so, C16 v) {
-        __builtin_amdgcn_raw_buffer_store_b16(v.bits, r, vo, so, 0);
+        __builtin_amdgcn_raw_buffer_store_b16(v.bits, r, vo, so, POLICY);
     }
 };
 // Store the lower half of a word (the form the 16-bit encode_sr functions return).
+template <int POLICY = WRITE_BACK>
 __device__ __forceinline__ void store_lo16(Rsrc r, uint32_t vo, uint32_t so, uint32_t w) {
-    __builtin_amdgcn_raw_buffer_store_b16((uint16_t)w, r, vo, so, 0);
+    __builtin_amdgcn_raw_buffer_store_b16((uint16_t)w, r, vo, so, POLICY);
 }
 template <>
 struct Buf<uint16_t> {
@@ -1193,7 +1207,10 @@ __global__ __launch_bounds__(TILE_LANES *R *C, sizeof(typename Codec<T>::AT) == 
 // two rows (24 output rows of 32; FP32 arithmetic) repeat fewer halo rows.  OCC = 8 wavefronts per
 // SIMD holds the kernel to 64 vector and 78 scalar registers, so that two blocks share a CU, one
 // loading while the other computes (44 channels of 630 x 60 in binary16: 45 us a step against 54).
-template <class T, int K, int OCC, bool WV>
+// What bounds it, on a 200 x 100 droplet (FP64, 52 blocks, 7.8 us a step; the march took 17): one
+// block's chain of loads, five stages and four barriers, and the 1.3 us between two launches; on
+// the 44 channels (42 us, 1.7 M nodes) the vector units and the waits of two blocks per CU.
+template <class T, int K, int OCC, int POLICY, bool WV>
 __global__ __launch_bounds__(TILE_LANES *PATCH_WAVES, OCC) void patch_kernel(const StepArgs<T, typename Codec<T>::AT> A) {
     using AT = typename Codec<T>::AT;
     constexpr int TX = TILE_LANES, TY = PATCH_WAVES * K, H = PATCH_HALO;
@@ -1515,16 +1532,24 @@ __global__ __launch_bounds__(TILE_LANES *PATCH_WAVES, OCC) void patch_kernel(con
         const uint32_t self = rows[k + 1] + (uint32_t)xe;
         const uint32_t vf = out ? self * SB : NOWHERE, vc = out ? self * CB : NOWHERE;
         const uint32_t rb = sizeof(T) == 2 ? round_bits((self - (uint32_t)D.off) * SB, o[0]) : 0u;
+        // Two rows a wavefront: all values are encoded first, so that the stores follow each other
+        // closely (60 channels of the sweep, binary16 / c16: 317 / 323 us a step against 320 / 329;
+        // with one row 7.67 against 7.57 on a capillary).
+        constexpr bool together = sizeof(T) == 2 && K > 1;
+        uint32_t code[9];
+        if constexpr (together)
+#pragma unroll
+            for (int a = 0; a < 9; a++) code[a] = Codec<T>::encode_sr(o[a], a, rb);
 #pragma unroll
         for (int a = 0; a < 9; a++) {
             if constexpr (sizeof(T) == 2)
-                store_lo16(f_out, vf, (uint32_t)a * FP, Codec<T>::encode_sr(o[a], a, rb));
+                store_lo16<POLICY>(f_out, vf, (uint32_t)a * FP, together ? code[a] : Codec<T>::encode_sr(o[a], a, rb));
             else
-                Buf<T>::store(f_out, vf, (uint32_t)a * FP, Codec<T>::encode(o[a], a));
+                Buf<T>::template store<POLICY>(f_out, vf, (uint32_t)a * FP, Codec<T>::encode(o[a], a));
         }
-        Buf<AT>::store(c_out, vc, 0, c);
-        Buf<AT>::store(c_out, vc, CP, bx);
-        Buf<AT>::store(c_out, vc, 2 * CP, by);
+        Buf<AT>::template store<POLICY>(c_out, vc, 0, c);
+        Buf<AT>::template store<POLICY>(c_out, vc, CP, bx);
+        Buf<AT>::template store<POLICY>(c_out, vc, 2 * CP, by);
     }
     if (bad) atomicOr(A.flag, 1);
 }
@@ -2342,6 +2367,37 @@ __global__ __launch_bounds__(CROSS_THREADS) void crossing_kernel(
 // their few spilled registers only cost (200 x 100 droplet 8.04 against 8.34 us a step, 52 items;
 // 2000 x 100 channel, 468 items, 16.5 against 15.7, 44 channels, 4224 items, 123 against 110).
 constexpr int PATCH64_ROOMY_ITEMS = 256;
+// Cache policy of the patch kernel's stores, by the bytes of the state (both copies) against the
+// 256 MB last-level cache.  While that holds the state, lines written through the L2 during the
+// kernel need no flush at its end and cost no more; beyond it, partial lines written through reach
+// HBM one by one.  FP64 lines, seldom partial, are better streamed past the L2 once enough of the
+// state no longer fits.  The 16-bit storages gain nothing.  us per step on channels of 630 x 60
+// (MI355X), write-back / write-through / stream:
+//   FP64  45 MB 19.8 / 19.3 / 19.6, 180 MB 50.2 / 48.9 / 64.3, 270 MB 84.4 / 90.4 / 86.5,
+//         330 MB 106.5 / 113.7 / 102.1, 435 MB 137.7 / 147.9 / 132.9
+//   FP32  82 MB 27.3 / 26.4 / 31.1, 165 MB 42.7 / 42.6 / 53.5, 247 MB 62.0 / 72.5 / 76.0,
+//         330 MB 98.6 / 111.2 / 98.0
+//   binary16  155 MB 58.8 / 59.0 / 69.4, 206 MB 73.9 / 74.6 / 88.4, 412 MB 168 / 191 / 172
+constexpr size_t THROUGH_BYTES = (size_t)192 << 20, STREAM_BYTES = (size_t)300 << 20;
+template <class T>
+static int store_policy(size_t plane) {
+    const size_t state = 2 * plane * (9 * sizeof(T) + 3 * sizeof(typename Codec<T>::AT));
+    if (sizeof(T) > 2 && state <= THROUGH_BYTES) return WRITE_THROUGH;
+    return sizeof(T) == 8 && state >= STREAM_BYTES ? WRITE_STREAM : WRITE_BACK;
+}
+
+template <class T, bool WV, int POLICY>
+static void patch_t(const StepArgs<T, typename Codec<T>::AT> &A, int n_items, const TileShape &t, hipStream_t s) {
+    constexpr bool f64 = sizeof(T) == 8;
+    const dim3 grid(n_items), block(TILE_LANES * PATCH_WAVES);
+    if (f64 && POLICY == WRITE_THROUGH && n_items <= PATCH64_ROOMY_ITEMS)
+        hipLaunchKernelGGL((patch_kernel<T, 1, f64 && POLICY == WRITE_THROUGH ? 4 : 8, POLICY, WV>), grid, block, 0, s, A);
+    else if (f64 || t.chunk == PATCH_ROWS)
+        hipLaunchKernelGGL((patch_kernel<T, 1, 8, POLICY, WV>), grid, block, 0, s, A);
+    else
+        hipLaunchKernelGGL((patch_kernel<T, f64 ? 1 : 2, 8, POLICY, WV>), grid, block, 0, s, A);
+}
+
 template <class T, bool WV>
 static hipError_t step_t(const void *args, int n_items, const TileShape &t, hipStream_t s) {
     const auto &A = *static_cast<const StepArgs<T, typename Codec<T>::AT> *>(args);
@@ -2357,13 +2413,11 @@ static hipError_t step_t(const void *args, int n_items, const TileShape &t, hipS
     if (t.npl != 1) return hipErrorInvalidValue;
     constexpr bool f64 = sizeof(typename Codec<T>::AT) == 8;
     if (t.patch(f64)) {
-        const dim3 grid(n_items), block(TILE_LANES * PATCH_WAVES);
-        if (f64 && n_items <= PATCH64_ROOMY_ITEMS)
-            hipLaunchKernelGGL((patch_kernel<T, 1, f64 ? 4 : 8, WV>), grid, block, 0, s, A);
-        else if (f64 || t.chunk == PATCH_ROWS)
-            hipLaunchKernelGGL((patch_kernel<T, 1, 8, WV>), grid, block, 0, s, A);
-        else
-            hipLaunchKernelGGL((patch_kernel<T, f64 ? 1 : 2, 8, WV>), grid, block, 0, s, A);
+        constexpr bool wide = sizeof(T) > 2;
+        const int policy = store_policy<T>(A.plane);
+        if (policy == WRITE_THROUGH) patch_t<T, WV, wide ? WRITE_THROUGH : WRITE_BACK>(A, n_items, t, s);
+        else if (policy == WRITE_STREAM) patch_t<T, WV, f64 ? WRITE_STREAM : WRITE_BACK>(A, n_items, t, s);
+        else patch_t<T, WV, WRITE_BACK>(A, n_items, t, s);
     }
     else if (t.cols == 2)
         hipLaunchKernelGGL((step_kernel<T, 4, 2, WV>), dim3(n_items), dim3(TILE_LANES * 8), 0, s, A);
