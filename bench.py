@@ -168,15 +168,21 @@ def roofline_of(storage, fluid, ms_per_step, workload=None, traffic_path=None, t
     """Roofline record of the step launch: algorithmic bytes over the event-timed launch, and the
     counter-measured HBM bytes when a profile of this kernel source, workload, storage and tile
     shape exists.  `tile` is the lattice's tile dict (the two-column kernel when
-    cols_per_lane = 2)."""
+    cols_per_lane = 2; the patch kernel for work items of 8 rows, or 24 with FP32 arithmetic, on
+    blocks of 8)."""
     bpl = BYTES_PER_LUP[storage]
     achieved = bpl * fluid / (ms_per_step * 1e-3) / 1e9
     traffic = None
     if workload is not None:
         traffic = measured_traffic(traffic_path or os.path.join(
             ROOT, "profiles", f"step_kernel_{workload}_{storage}_hbm_bytes.md"), workload, storage, tile)
-    pair = bool(tile) and tile.get("cols_per_lane", 1) == 2
-    kernel = f"pair_kernel<{KERNEL[storage]}>" if pair else f"step_kernel<{KERNEL[storage]}>"
+    kernel = "step_kernel"
+    if tile and tile.get("cols_per_lane", 1) == 2:
+        kernel = "pair_kernel"
+    elif tile and (tile.get("waves"), tile.get("cols")) == (8, 1) and \
+            tile.get("chunk_rows") in ((8,) if storage == "f64" else (8, 24)):
+        kernel = "patch_kernel"
+    kernel = f"{kernel}<{KERNEL[storage]}>"
     return dict(bound="hbm", achieved=round(achieved, 1), peak=HBM_PEAK_GBS, unit="GB/s",
                 frac=round(achieved / HBM_PEAK_GBS, 4), traffic=traffic,
                 kernel=kernel, bytes_per_lup=bpl, lups_per_launch=fluid)
