@@ -436,8 +436,8 @@ int auto_chunk(const std::vector<lbm_domain_desc> &d, TileShape t, int storage) 
 // every storage type.
 constexpr int DEFAULT_WAVES = 4;
 // One-wavefront tiles.  Tiles two wavefronts wide (120 output columns of 128; 118 with FP64
-// arithmetic) repeat fewer halo columns but measured 3-5 % slower on the sweep (8-wavefront
-// barriers, 2 blocks per CU).
+// arithmetic) repeat fewer halo columns but measured 11 % slower on the sweep (1.75 against 1.57 ms
+// a step in binary16: 8-wavefront barriers, 2 blocks per CU).
 constexpr int DEFAULT_COLS = 1;
 // The built-in shape of a batch: the patch kernel, which takes a work item at once, while its
 // repeated halo rows cost less than the march's iterations (us per step on an MI355X, patch
@@ -461,7 +461,7 @@ TileShape builtin_tile(const std::vector<lbm_domain_desc> &d, int storage) {
 // The pair kernel (two node columns per lane) needs FP32 arithmetic and an even width in every
 // domain.  It is offered to lbm_set_tile and the autotuner but is not the built-in choice: at the
 // two wavefronts per SIMD its register use allows, it measured slower than the one-column kernel
-// at four (binary16 sweep 33.9 against 50.7 GLUPS).
+// at five (binary16 sweep 45.9 against 52.6 GLUPS).
 bool pair_allowed(int storage, const std::vector<lbm_domain_desc> &d) {
     if (storage == 0) return false;
     for (const auto &q : d)
