@@ -547,8 +547,8 @@ int create_t(lbm_ctx *c, const lbm_domain_desc *d) {
         D.wetting = q.wetting;
         D.io_off = io;
         DomPar<double> &PD = D.d;
-        PD.inv_nu_sum = 1.0 / (2.0 * q.nu_r) + 1.0 / (2.0 * q.nu_b);
-        PD.inv_nu_diff = 1.0 / (2.0 * q.nu_r) - 1.0 / (2.0 * q.nu_b);
+        PD.inv2nu_r = 1.0 / (2.0 * q.nu_r);
+        PD.inv2nu_b = 1.0 / (2.0 * q.nu_b);
         PD.half_sigma = 0.5 * q.sigma;
         PD.beta = q.beta;
         PD.cos_t = std::cos(th);

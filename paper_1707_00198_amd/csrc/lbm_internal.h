@@ -45,11 +45,11 @@ struct TileShape {
 
 // Per-domain parameters in one arithmetic type, with the constant factors of the collision
 // precomputed: ke = 6 (1 - s_e / 2), keps = 6 (1 - s_eps / 2), kq = 1 - s_q / 2 (the forcing
-// terms of Eq. 8 for e, epsilon and q), 1/nu of Eq. 18 as inv_nu_sum + inv_nu_diff rho^N, and
-// w_a rho0 of the rest, axis and diagonal directions.
+// terms of Eq. 8 for e, epsilon and q), 1 / (2 nu) of either phase (Eq. 18), and w_a rho0 of the
+// rest, axis and diagonal directions.
 template <class AT>
 struct DomPar {
-    AT rho0, eps, inv_nu_sum, inv_nu_diff, half_sigma, beta, cos_t, sin_t;
+    AT rho0, eps, inv2nu_r, inv2nu_b, half_sigma, beta, cos_t, sin_t;
     AT s_e, s_eps, s_q, ke, keps, kq, outlet_u, w_rest;
     AT w_axis, w_diag, pad[2];
 };

@@ -616,8 +616,11 @@ __device__ __forceinline__ void collide(ParC<AT> &P, const AT d[9], AT Fx, AT Fy
     const AT px = AT(0.5) * Fx + jx, py = AT(0.5) * Fy + jy;  // rho u
     ux = px * ir;
     uy = py * ir;
-    // Eqs. 18 and 5: 1/nu interpolated in rho^N, tau = 3 nu + 1/2, s_nu = 1/tau
-    const AT inv_nu = rN * P.inv_nu_diff + P.inv_nu_sum;
+    // Eqs. 18 and 5: 1/nu interpolated in rho^N, tau = 3 nu + 1/2, s_nu = 1/tau.  As two products:
+    // a sum and a difference of the two constants would cancel in the more viscous phase, for a
+    // relative error of one unit times the viscosity ratio.
+    const AT inv_nu_b = (AT(1) - rN) * P.inv2nu_b;
+    const AT inv_nu = (AT(1) + rN) * P.inv2nu_r + inv_nu_b;
     const AT sv = inv_nu * rcp(AT(0.5) * inv_nu + AT(3));
     const AT qx = px * ux, qy = py * uy;
     const AT r3 = AT(3) * (qx + qy), exx = qx - qy, exy = px * uy;

@@ -1,0 +1,127 @@
+"""The device code's node arithmetic on the CPU, against extended precision.
+
+The sections of csrc/lbm_kernels.hip that hold the arithmetic of one node, and the lines of
+csrc/lbm_host.cpp that fill a domain's parameters, are compiled as they stand for the host.  The
+hardware's estimates are replaced by what they promise at best: the FP64 reciprocal by one of 24
+bits, the FP32 reciprocal and square roots by correctly rounded ones.
+"""
+import ctypes as C
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1707_00198_amd", "csrc")
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+
+HEAD = r"""
+#include <cmath>
+#include <cstdint>
+#include <cstring>
+#include "lbm_internal.h"
+#undef __device__
+#undef __forceinline__
+#define __device__
+#define __forceinline__ inline
+using namespace lbmcg;
+using std::sqrt;
+#define fsqrt node_fsqrt  // the C library has an fsqrt of its own
+static double est_rcp(double x) { int e; const double m = std::frexp(x, &e); return std::ldexp((double)(float)(1.0 / m), -e); }
+#define __builtin_amdgcn_rcp(x) est_rcp(x)
+#define __builtin_amdgcn_rcpf(x) (float)(1.0 / (double)(x))
+#define __builtin_amdgcn_sqrtf(x) (float)std::sqrt((double)(x))
+#define __builtin_amdgcn_rsqf(x) (float)(1.0 / std::sqrt((double)(x)))
+template <class AT> using ParC = const DomPar<AT>;
+"""
+
+TAIL = r"""
+struct Q { double nu_r, nu_b, sigma, beta, theta_deg, s_e, s_eps, s_q, rho0, eps, outlet_u; };
+static const double WH[9] = {4.0 / 9, 1.0 / 9, 1.0 / 9, 1.0 / 9, 1.0 / 9, 1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36};
+static void fill(const Q &q, DomDev &D) {
+    const double th = q.theta_deg * M_PI / 180.0;
+    %FILL%
+}
+static const DomPar<double> &of(const DomDev &D, double) { return D.d; }
+static const DomPar<float> &of(const DomDev &D, float) { return D.f; }
+// post-collision deviations and velocity of n nodes of one pure phase (red = 1 or blue = 0), no force
+template <class AT> static void nodes(const Q *q, int n, const AT *d, int red, AT *o, AT *u) {
+    DomDev D{};
+    fill(*q, D);
+    for (int i = 0; i < n; i++) {
+        AT rR, rB, c, bx, by;
+        gather_interior(of(D, AT()), d + 9 * i, AT(red), rR, rB, [&](int, bool, AT &cs, AT &ev) { cs = AT(red); ev = AT(0); });
+        collide(of(D, AT()), d + 9 * i, AT(0), AT(0), colour_indicator(rR, rB), rR, rB, AT(0), AT(0),
+                *reinterpret_cast<AT (*)[9]>(o + 9 * i), u[2 * i], u[2 * i + 1], c, bx, by);
+    }
+}
+extern "C" {
+void nodes_f64(const Q *q, int n, const double *d, int red, double *o, double *u) { nodes(q, n, d, red, o, u); }
+void nodes_f32(const Q *q, int n, const float *d, int red, float *o, float *u) { nodes(q, n, d, red, o, u); }
+void normals_f64(int n, const double *g, double eps, double *out) {
+    for (int i = 0; i < n; i++) unit_normal(g[2 * i], g[2 * i + 1], eps, out[3 * i], out[3 * i + 1], out[3 * i + 2]);
+}
+void normals_f32(int n, const float *g, float eps, float *out) {
+    for (int i = 0; i < n; i++) unit_normal(g[2 * i], g[2 * i + 1], eps, out[3 * i], out[3 * i + 1], out[3 * i + 2]);
+}
+void quotients(int n, const double *a, const double *b, double *out) {
+    for (int i = 0; i < n; i++) out[i] = quotient(a[i], b[i], rcp(b[i]));
+}
+}
+"""
+
+
+class Q(C.Structure):
+    _fields_ = [(k, C.c_double) for k in ("nu_r", "nu_b", "sigma", "beta", "theta_deg", "s_e", "s_eps", "s_q", "rho0",
+                                          "eps", "outlet_u")]
+
+
+def _between(text, first, last):
+    i = text.index(first)
+    return text[i:text.index(last, i)]
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    k = open(os.path.join(CSRC, "lbm_kernels.hip")).read()
+    h = open(os.path.join(CSRC, "lbm_host.cpp")).read()
+    code = HEAD + _between(k, "// D2Q9 velocity set", "// ------------------------------------------------------------------ storage codec")
+    code += _between(k, "// e_a . v of a colour state", "// Completes the post-streaming populations")
+    code += _between(k, "// MRT collision with Guo forcing", "// Work item of block b")
+    code += TAIL.replace("%FILL%", _between(h, "DomPar<double> &PD = D.d;", "int n_fluid_bnd = 0;"))
+    d = tmp_path_factory.mktemp("node")
+    src, so = str(d / "node.cpp"), str(d / "node.so")
+    with open(src, "w") as f:
+        f.write(code)
+    subprocess.check_call([os.path.join(ROCM, "llvm", "bin", "clang++"), "-std=c++17", "-O2", "-mfma", "-fPIC", "-shared", "-w",
+                           "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROCM, "include"), "-I", CSRC, "-o", so, src])
+    return C.CDLL(so)
+
+
+def _params(nu_r, nu_b):
+    return Q(nu_r, nu_b, 0.01, 0.7, 90.0, 1.64, 1.54, 1.9, 1.0, 1e-10, 0.0)
+
+
+def _nodes(lib, q, d, red):
+    o, u = np.empty_like(d), np.empty((len(d), 2), d.dtype)
+    p = lambda a: a.ctypes.data_as(C.c_void_p)  # noqa: E731
+    (lib.nodes_f64 if d.dtype == np.float64 else lib.nodes_f32)(C.byref(q), len(d), p(d), red, p(o), p(u))
+    return o, u
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("nu,ratio", [(0.3, 1000.0), (0.45, 1000.0), (0.137, 1000.0), (1.0 / 6.0, 50.0), (0.35, 100.0)])
+def test_viscosity_of_a_pure_phase(lib, nu, ratio, dtype):
+    """s_nu of either pure phase, whichever is the viscous one, from a node that holds nothing but
+    the normal stress m_7.  Rounded are the stored 1/(2 nu) (half a unit), the sum with 3, the
+    product and the step's own m_7 (half a unit each) and the reciprocal (one): 4 units, with u the
+    spacing at 1."""
+    a = dtype(2.0 ** -6)
+    d = np.array([[0, a, -a, a, -a, 0, 0, 0, 0]], dtype)
+    for red in (1, 0):
+        o, _ = _nodes(lib, _params(*((nu, nu / ratio) if red else (nu / ratio, nu))), d, red)
+        m7 = np.longdouble(o[0, 1]) - o[0, 2] + o[0, 3] - o[0, 4]
+        s = 1 - m7 / (4 * np.longdouble(a))
+        want = 1 / (3 * np.longdouble(nu) + np.longdouble(0.5))
+        assert abs(s / want - 1) <= 4 * np.finfo(dtype).eps, (red, float(s / want - 1))
