@@ -66,7 +66,7 @@ __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x);
 __device__ __forceinline__ double fsqrt(double x) { return sqrt(x); }
 __device__ __forceinline__ float fsqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
 
-// a / b with ib = rcp(b), corrected by the residual: exactly 1 for a = b and free of the
+// a / b with ib within a few units of 1 / b, corrected by the residual: exactly 1 for a = b and free of the
 // reciprocal's systematic bias (the red fraction c = rho_R / rho must not drift the colour
 // masses); in FP64 the correctly rounded quotient but for rare last-bit cases.
 template <class AT>
@@ -434,6 +434,11 @@ __device__ __forceinline__ void gather_interior(ParC<AT> &P, const AT d[9], AT c
         const int a = PULL_ORDER[k];
         colour(a, false, c, ev);
         add_pull(a, (a < 5 ? P.w_axis : P.w_diag) + d[a], c, ev, rR, tot);
+        // FP64: the total's first half before the red density's second.  Left to itself the compiler
+        // sums the total last, from eight populations kept until then, and the 64-register patches
+        // spill 6 of them (44 channels of 630 x 60: 113 us a step against 98; a tie after every
+        // second pull 98, after the last 103.5).
+        if (sizeof(AT) == 8 && k == 3) asm("" : "+v"(rR), "+v"(tot));
     }
     const AT f0 = P.w_rest + d[0];
     const AT r0 = cself * f0;
@@ -595,7 +600,9 @@ __device__ __forceinline__ void wetting_correct(AT nsx, AT nsy, AT ct, AT st, AT
 // post-collision deviations in o, the velocity of Eq. 17 and the new colour state (c, v) for the
 // interface normal n (Eq. 14).  Opposite populations are summed and subtracted first and the
 // moments built from those (24 operations), rho u is kept as the momentum rather than rebuilt
-// from u, and one reciprocal of the density serves the velocity and the red fraction.
+// from u, and one reciprocal of the density serves the velocity and the red fraction: that of rho0
+// plus the deviations, which carries fewer roundings than rR + rB (the red fraction's quotient
+// then takes its residual against rR + rB).
 template <class AT>
 __device__ __forceinline__ void collide(ParC<AT> &P, const AT d[9], AT Fx, AT Fy, AT rN, AT rR, AT rB,
                                         AT nx, AT ny, AT o[9], AT &ux, AT &uy, AT &c, AT &bx, AT &by) {
@@ -611,8 +618,7 @@ __device__ __forceinline__ void collide(ParC<AT> &P, const AT d[9], AT Fx, AT Fy
     const AT m4 = ex - AT(2) * dx, m6 = ey - AT(2) * dy;
     const AT m7 = s1 - s2, m8 = t1 - t2;
 
-    const AT rs = rR + rB;
-    const AT ir = rcp(rs);
+    const AT ir = rcp(P.rho0 + drho);
     const AT px = AT(0.5) * Fx + jx, py = AT(0.5) * Fy + jy;  // rho u
     ux = px * ir;
     uy = py * ir;
@@ -660,7 +666,7 @@ __device__ __forceinline__ void collide(ParC<AT> &P, const AT d[9], AT Fx, AT Fy
     o[8] = dm + km;
     o[6] = dm - km;
     // recolouring state (Eq. 14)
-    c = quotient(rR, rs, ir);
+    c = quotient(rR, rR + rB, ir);
     const AT b = P.beta * rB * c;
     bx = b * nx;
     by = b * ny;

@@ -45,15 +45,16 @@ static void fill(const Q &q, DomDev &D) {
 }
 static const DomPar<double> &of(const DomDev &D, double) { return D.d; }
 static const DomPar<float> &of(const DomDev &D, float) { return D.f; }
-// post-collision deviations and velocity of n nodes of one pure phase (red = 1 or blue = 0), no force
+// post-collision deviations, velocity and red fraction of n nodes of one pure phase (red = 1 or blue
+// = 0), no force
 template <class AT> static void nodes(const Q *q, int n, const AT *d, int red, AT *o, AT *u) {
     DomDev D{};
     fill(*q, D);
     for (int i = 0; i < n; i++) {
-        AT rR, rB, c, bx, by;
+        AT rR, rB, bx, by;
         gather_interior(of(D, AT()), d + 9 * i, AT(red), rR, rB, [&](int, bool, AT &cs, AT &ev) { cs = AT(red); ev = AT(0); });
         collide(of(D, AT()), d + 9 * i, AT(0), AT(0), colour_indicator(rR, rB), rR, rB, AT(0), AT(0),
-                *reinterpret_cast<AT (*)[9]>(o + 9 * i), u[2 * i], u[2 * i + 1], c, bx, by);
+                *reinterpret_cast<AT (*)[9]>(o + 9 * i), u[3 * i], u[3 * i + 1], u[3 * i + 2], bx, by);
     }
 }
 extern "C" {
@@ -104,7 +105,7 @@ def _params(nu_r, nu_b):
 
 
 def _nodes(lib, q, d, red):
-    o, u = np.empty_like(d), np.empty((len(d), 2), d.dtype)
+    o, u = np.empty_like(d), np.empty((len(d), 3), d.dtype)
     p = lambda a: a.ctypes.data_as(C.c_void_p)  # noqa: E731
     (lib.nodes_f64 if d.dtype == np.float64 else lib.nodes_f32)(C.byref(q), len(d), p(d), red, p(o), p(u))
     return o, u
@@ -125,3 +126,19 @@ def test_viscosity_of_a_pure_phase(lib, nu, ratio, dtype):
         s = 1 - m7 / (4 * np.longdouble(a))
         want = 1 / (3 * np.longdouble(nu) + np.longdouble(0.5))
         assert abs(s / want - 1) <= 4 * np.finfo(dtype).eps, (red, float(s / want - 1))
+
+
+def test_velocity_takes_the_density_from_the_deviations(lib):
+    """Deviations that are multiples of 2^-20 below 1/8: their sums, and 1 plus their sum, are exact
+    in FP32, so the velocity of a force-free node carries the roundings of the reciprocal and of
+    the product alone, half a unit each.  The sum of nine populations w_a + d_a, each rounded, would
+    bring its own.  The red fraction, by the same reciprocal, is exactly 1."""
+    rng = np.random.default_rng(11)
+    d = (rng.integers(-2 ** 17, 2 ** 17, (20000, 9)) * 2.0 ** -20).astype(np.float32)
+    e = np.array([[0, 0], [1, 0], [0, 1], [-1, 0], [0, -1], [1, 1], [-1, 1], [-1, -1], [1, -1]], np.float64)
+    _, u = _nodes(lib, _params(0.5, 0.25), d, 1)
+    want = (d.astype(np.float64) @ e) / (1.0 + d.astype(np.float64).sum(axis=1))[:, None]
+    assert (u[:, 2] == 1).all()
+    some = np.abs(want) > 0
+    err = np.abs(u[:, :2][some] / want[some] - 1.0)
+    assert err.max() <= np.finfo(np.float32).eps * (1 + 2.0 ** -20), err.max()
