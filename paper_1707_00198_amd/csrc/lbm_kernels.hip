@@ -53,9 +53,9 @@ __device__ __forceinline__ AT wgt(int a) {
     return a == 0 ? AT(4.0 / 9.0) : (a < 5 ? AT(1.0 / 9.0) : AT(1.0 / 36.0));
 }
 
-// Reciprocal of a density, a viscosity or a weight sum (positive, of order one).  FP64: the
-// hardware's estimate with two Newton steps, within one ulp, in 5 instructions where the IEEE
-// division takes 12 to also cover operands near the ends of the exponent range; FP32: the
+// Reciprocal of a density, a viscosity, a modulus or a weight sum.  FP64: the hardware's estimate
+// with two Newton steps, correctly rounded but for rare last-bit cases, in 5 instructions where the
+// IEEE division takes 12 to also cover operands near the ends of the exponent range; FP32: the
 // hardware's 1-ulp instruction.
 __device__ __forceinline__ double rcp(double x) {
     double r = __builtin_amdgcn_rcp(x);
@@ -98,8 +98,8 @@ __device__ __forceinline__ void unit_normal(double gx, double gy, double eps, do
     g = sqrt(g2);
     const bool on = g > eps;
     const double ig = rcp(g);
-    nx = on ? gx * ig : 0.0;
-    ny = on ? gy * ig : 0.0;
+    nx = on ? quotient(gx, g, ig) : 0.0;
+    ny = on ? quotient(gy, g, ig) : 0.0;
 }
 __device__ __forceinline__ void unit_normal(float gx, float gy, float eps, float &g, float &nx,
                                             float &ny) {

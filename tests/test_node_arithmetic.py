@@ -142,3 +142,23 @@ def test_velocity_takes_the_density_from_the_deviations(lib):
     some = np.abs(want) > 0
     err = np.abs(u[:, :2][some] / want[some] - 1.0)
     assert err.max() <= np.finfo(np.float32).eps * (1 + 2.0 ** -20), err.max()
+
+
+def test_fp64_divisions_round_as_the_ieee_division(lib):
+    """Quotients by Newton steps and a residual correction: two steps from an estimate of 24 bits
+    leave 2^-90 before the last rounding, so a quotient differs from the correctly rounded one only
+    where that lies within about 2^-38 units of a tie (none in 1e5 to expect).  The unit normal is
+    the gradient over the modulus that comes with it, 0 up to the threshold."""
+    rng = np.random.default_rng(5)
+    n = 100000
+    p = lambda a: a.ctypes.data_as(C.c_void_p)  # noqa: E731
+    a, b, out = rng.uniform(-1.0, 1.0, n), rng.uniform(0.5, 2.0, n), np.empty(n)
+    lib.quotients(n, p(a), p(b), p(out))
+    assert np.array_equal(out, a / b)
+    g, r = rng.uniform(-1.0, 1.0, (n, 2)) * 10.0 ** rng.uniform(-9.0, 0.0, (n, 1)), np.empty((n, 3))
+    lib.normals_f64(n, p(g), C.c_double(1e-10), p(r))
+    assert np.array_equal(r[:, 1:], np.where(r[:, :1] > 1e-10, g / r[:, :1], 0.0))
+    # below the threshold, and where there is no gradient at all
+    g, r = np.array([[0.0, 0.0], [6e-11, -7e-11], [0.0, -1e-10]]), np.empty((3, 3))
+    lib.normals_f64(3, p(g), C.c_double(1e-10), p(r))
+    assert np.array_equal(r[:, 1:], np.zeros((3, 2)))
