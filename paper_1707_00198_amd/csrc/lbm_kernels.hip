@@ -90,7 +90,8 @@ __device__ __forceinline__ float colour_indicator(float rR, float rB) {
 // bits from every kernel and tile shape, whatever the compiler could fuse around it.
 
 // Modulus g and unit normal (Eq. 22) of a gradient; n = 0 where g <= eps.  FP32: one
-// reciprocal square root gives both (g = 0 gives 0 * inf = NaN, which fails the test too).
+// reciprocal square root gives both, at most 2^63: that of the smallest normal square, below which
+// the instruction takes the square for 0 and gives infinity.
 __device__ __forceinline__ void unit_normal(double gx, double gy, double eps, double &g, double &nx,
                                             double &ny) {
 #pragma clang fp contract(on)
@@ -105,7 +106,7 @@ __device__ __forceinline__ void unit_normal(float gx, float gy, float eps, float
                                             float &ny) {
 #pragma clang fp contract(on)
     const float g2 = gx * gx + gy * gy;
-    const float ig = __builtin_amdgcn_rsqf(g2);
+    const float ig = fminf(__builtin_amdgcn_rsqf(g2), 0x1p63f);
     g = g2 * ig;
     const bool on = g > eps;
     g = on ? g : 0.0f;

@@ -3,7 +3,8 @@
 The sections of csrc/lbm_kernels.hip that hold the arithmetic of one node, and the lines of
 csrc/lbm_host.cpp that fill a domain's parameters, are compiled as they stand for the host.  The
 hardware's estimates are replaced by what they promise at best: the FP64 reciprocal by one of 24
-bits, the FP32 reciprocal and square roots by correctly rounded ones.
+bits, the FP32 reciprocal and square roots by correctly rounded ones, which take subnormals for 0 as
+the instructions do.
 """
 import ctypes as C
 import os
@@ -30,9 +31,10 @@ using std::sqrt;
 #define fsqrt node_fsqrt  // the C library has an fsqrt of its own
 static double est_rcp(double x) { int e; const double m = std::frexp(x, &e); return std::ldexp((double)(float)(1.0 / m), -e); }
 #define __builtin_amdgcn_rcp(x) est_rcp(x)
-#define __builtin_amdgcn_rcpf(x) (float)(1.0 / (double)(x))
-#define __builtin_amdgcn_sqrtf(x) (float)std::sqrt((double)(x))
-#define __builtin_amdgcn_rsqf(x) (float)(1.0 / std::sqrt((double)(x)))
+static double flush(float x) { return std::fabs(x) < 0x1p-126f ? std::copysign(0.0, (double)x) : (double)x; }
+#define __builtin_amdgcn_rcpf(x) (float)(1.0 / flush(x))
+#define __builtin_amdgcn_sqrtf(x) (float)std::sqrt(flush(x))
+#define __builtin_amdgcn_rsqf(x) (float)(1.0 / std::sqrt(flush(x)))
 template <class AT> using ParC = const DomPar<AT>;
 """
 
@@ -162,3 +164,24 @@ def test_fp64_divisions_round_as_the_ieee_division(lib):
     g, r = np.array([[0.0, 0.0], [6e-11, -7e-11], [0.0, -1e-10]]), np.empty((3, 3))
     lib.normals_f64(3, p(g), C.c_double(1e-10), p(r))
     assert np.array_equal(r[:, 1:], np.zeros((3, 2)))
+
+
+def test_fp32_normals(lib):
+    """The FP32 modulus and normal against FP64: half a unit from the square's sum and its two products
+    each (the root halves them), one from the reciprocal root and half from the product.  Gradients
+    whose square is subnormal or 0 are below any threshold that single precision can tell from 0."""
+    rng = np.random.default_rng(6)
+    n = 100000
+    p = lambda a: a.ctypes.data_as(C.c_void_p)  # noqa: E731
+    g, r = (rng.uniform(-1.0, 1.0, (n, 2)) * 10.0 ** rng.uniform(-9.0, 0.0, (n, 1))).astype(np.float32), np.empty((n, 3), np.float32)
+    lib.normals_f32(n, p(g), C.c_float(1e-10), p(r))
+    m = np.hypot(*g.astype(np.float64).T)
+    on = m > 1.1e-10
+    want = np.column_stack([m, g / m[:, None]])[on]
+    assert np.abs(r[on] - want).max(axis=0)[1:].max() <= 3 * 2.0 ** -23 and (np.abs(r[on, 0] / m[on] - 1) <= 3 * 2.0 ** -23).all()
+    g = (rng.uniform(-1.0, 1.0, (n, 2)) * 10.0 ** rng.uniform(-25.0, -19.3, (n, 1))).astype(np.float32)
+    g[:3] = [[0, 0], [0, 1e-20], [1e-22, 0]]
+    lib.normals_f32(n, p(g), C.c_float(1e-10), p(r))
+    assert not r.any()
+    lib.normals_f32(n, p(g), C.c_float(1e-30), p(r))
+    assert np.isfinite(r).all() and np.abs(r[:, 1:]).max() <= 1.0 + 2.0 ** -22
