@@ -779,13 +779,20 @@ struct Buf<uint16_t> {
 // rows.  WV: some domain of the launch uses a wetting variant (Sec. III A); without it the
 // variant branches are compiled out.
 //
-// Wavefronts per SIMD (launch bounds): with FP32 arithmetic the kernel is held to 96 vector
-// registers, 5 wavefronts, with 4 to 7 of them in scratch; at 101 to 104 and 4 wavefronts, without
+// Wavefronts per SIMD (launch bounds) of blocks of 4: with FP32 arithmetic the kernel is held to 96
+// vector registers, 5 wavefronts, with 4 to 7 of them in scratch; at 101 to 104 and 4 wavefronts, without
 // scratch, a step takes 64.4 against 69.2 us on 44 channels of 630 x 60 in binary16, 68 against 72
 // on twelve 400 x 400 cylinder boxes in c16, 326 against 335 on 60 channels of the sweep; FP32 on
-// 16384 x 512 alone prefers 4 (246 against 250).  With FP64 arithmetic it needs 159, 3 wavefronts.
+// 16384 x 512 alone prefers 4 (246 against 250).  With FP64 arithmetic it needs 160, 3 wavefronts.
+// Blocks of 8 put 2 wavefronts on every SIMD, so 4 fit with FP32 arithmetic and 2 with FP64; held to
+// 96 registers they only spilled (44 channels in 16-row chunks on 8 x 1: 88.3 us a step against 85.3
+// in FP32, the 60 channels on 4 x 2 370 against 352 in binary16).
+constexpr int march_occupancy(size_t arithmetic_bytes, int block_waves) {
+    if (block_waves == 4) return arithmetic_bytes == 4 ? 5 : 3;
+    return arithmetic_bytes == 4 ? 4 : 2;
+}
 template <class T, int R, int C, bool WV>
-__global__ __launch_bounds__(TILE_LANES *R *C, sizeof(typename Codec<T>::AT) == 4 ? 5 : 3) void step_kernel(const StepArgs<T, typename Codec<T>::AT> A) {
+__global__ __launch_bounds__(TILE_LANES *R *C, march_occupancy(sizeof(typename Codec<T>::AT), R *C)) void step_kernel(const StepArgs<T, typename Codec<T>::AT> A) {
     using AT = typename Codec<T>::AT;
     constexpr int Q = 2 * R;
     constexpr int TL = TILE_LANES * C;  // columns of the window: C wavefronts side by side

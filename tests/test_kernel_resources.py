@@ -41,3 +41,13 @@ def test_patch_kernels_hold_their_values_in_registers(tmp_path):
     for name, (scratch, vgprs) in k.items():
         assert scratch <= (12 if "patch_kernelIdLi1ELi8E" in name and "Lb0E" in name else 0), (name, scratch, vgprs)
         assert vgprs <= 64 or "patch_kernelIdLi1ELi4E" in name, (name, vgprs)
+
+
+def test_blocks_of_eight_wavefronts_keep_their_registers(tmp_path):
+    """A block of 8 wavefronts puts 2 on each SIMD, so a CU holds 2 such blocks up to 128 vector
+    registers and none more down to 85: a tighter bound would only push values into scratch memory."""
+    k = {n: v for n, v in _kernels(tmp_path).items() if re.search(r"step_kernelI.*Li(8ELi1|4ELi2)ELb[01]E", n) and not n.endswith(".kd")}
+    assert len(k) == 16
+    for name, (scratch, vgprs) in k.items():
+        assert scratch == 0, (name, scratch, vgprs)
+        assert vgprs <= 128 or "step_kernelId" in name, (name, vgprs)
