@@ -152,8 +152,8 @@ int lbm_step(lbm_ctx *ctx, int64_t n_steps);
 int lbm_set_graph(lbm_ctx *ctx, int launches);
 
 /* Autotuner of the step's tile shape on this context's own batch: times every provided shape,
- * chunk_rows in {8, 12, 16, 24, 32, 48, 64} (shapes that cut no domain differently are timed
- * once) x (waves, cols, cols_per_lane) in {(4, 1, 1), (8, 1, 1), (4, 2, 1)}, plus (4, 1, 2) and
+ * chunk_rows in {8, 12, 16, 24, 32, 48, 64} (shapes that run the same kernel and cut no domain
+ * differently are timed once) x (waves, cols, cols_per_lane) in {(4, 1, 1), (8, 1, 1), (4, 2, 1)}, plus (4, 1, 2) and
  * (8, 1, 2) where lbm_set_tile allows two columns per lane, with `steps` (1..100000) timed steps
  * after one untimed step each, re-times the three fastest and keeps the fastest (as
  * lbm_set_tile).  The trials run real steps, so the state is first saved to `save_dev`

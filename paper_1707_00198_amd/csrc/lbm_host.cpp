@@ -767,11 +767,12 @@ int lbm_autotune(lbm_ctx *c, int steps, void *save_dev, double *out_host) {
     const bool pairs = pair_allowed(c->storage, c->desc);
     for (const auto &sh : shapes) {
         if (sh[2] == 2 && !pairs) continue;
-        std::vector<WorkItem> prev;
+        std::vector<WorkItem> last[2];  // of the march and of the patch kernel
         for (int ch : {8, 12, 16, 24, 32, 48, 64}) {
             const TileShape t{ch, sh[0], sh[1], sh[2]};
             std::vector<WorkItem> it = build_items(c->desc, t, c->storage);
-            // a taller chunk that cuts no domain differently is the same schedule
+            // a taller chunk that cuts no domain differently is the same schedule of its kernel
+            std::vector<WorkItem> &prev = last[t.patch(c->storage == 0)];
             if (it.size() == prev.size() &&
                 std::equal(it.begin(), it.end(), prev.begin(), [](const WorkItem &a, const WorkItem &b) {
                     return a.dom == b.dom && a.x0 == b.x0 && a.y0 == b.y0 && a.y1 == b.y1;

@@ -1,0 +1,135 @@
+"""The host's schedule without a GPU: the host source compiled against stand-ins for the HIP
+runtime (host memory, a clock that the test sets) and for the kernel launchers (which note the tile
+shape they are asked for), so that what lbm_create, lbm_set_tile and lbm_autotune choose can be seen."""
+import ctypes as C
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_1707_00198_amd import lbm
+from paper_1707_00198_amd import workloads as W
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1707_00198_amd", "csrc")
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+STAND_INS = r"""
+#include <cstdlib>
+#include <cstring>
+#include "lbm_internal.h"
+using namespace lbmcg;
+static TileShape last, fast;
+extern "C" {
+// shape that the clock calls twice as fast as any other
+void fast_shape(int chunk, int waves, int cols, int npl) { fast = TileShape{chunk, waves, cols, npl}; }
+hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t) { memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t) { memset(d, v, n); return hipSuccess; }
+hipError_t hipHostMalloc(void **p, size_t n, unsigned) { return (*p = malloc(n)) ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipHostFree(void *p) { free(p); return hipSuccess; }
+const char *hipGetErrorString(hipError_t) { return "stand-in"; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t *e) { *e = nullptr; return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) {
+    const bool f = last.chunk == fast.chunk && last.waves == fast.waves && last.cols == fast.cols && last.npl == fast.npl;
+    *ms = f ? 1.0f : 2.0f;
+    return hipSuccess;
+}
+hipError_t hipStreamCreateWithFlags(hipStream_t *, unsigned) { return hipErrorNotSupported; }
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipErrorNotSupported; }
+hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t *) { return hipErrorNotSupported; }
+hipError_t hipGraphInstantiateWithFlags(hipGraphExec_t *, hipGraph_t, unsigned long long) { return hipErrorNotSupported; }
+hipError_t hipGraphUpload(hipGraphExec_t, hipStream_t) { return hipErrorNotSupported; }
+hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipErrorNotSupported; }
+hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
+hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
+}
+namespace lbmcg {
+hipError_t noalloc_scratch(int, void **p) { *p = nullptr; return hipSuccess; }
+hipError_t launch_step(int, const void *, int, const TileShape &t, bool, hipStream_t) { last = t; return hipSuccess; }
+hipError_t launch_read(int, const void *, int, int, int, uint32_t, double *, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_mass(int, const void *, int, double *, int, double *, int *, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_velocity_stats(int, const void *, int, const void *, const void *, double *, double *, int *, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_velocity_copy(int, const void *, int, const void *, double *, double *, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_region_mass(int, const void *, int, const uint8_t *, double *, double *, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_crossings(int, const void *, int, int, const int *, int, double *, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_crossings_noalloc(int, const void *, int, int, void *, int, hipStream_t) { return hipErrorNotSupported; }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    d = tmp_path_factory.mktemp("host")
+    src, so = str(d / "stand_ins.cpp"), str(d / "host.so")
+    with open(src, "w") as f:
+        f.write(STAND_INS)
+    # no HIP runtime is linked: every runtime call goes to the stand-ins
+    subprocess.check_call([HIPCC, "-x", "hip", "--offload-host-only", "-no-hip-rt", "-std=c++17", "-O1", "-fPIC", "-shared", "-w",
+                           "-Wl,-Bsymbolic", "-Wl,--no-undefined", "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-o", so, src,
+                           os.path.join(CSRC, "lbm_host.cpp")])
+    L = C.CDLL(so)
+    for name, (res, args) in lbm.PROTOTYPES.items():
+        getattr(L, name).restype, getattr(L, name).argtypes = res, args
+    return L
+
+
+class Context:
+    """A context over `shapes` = [(nx, ny), ...], periodic, with its buffers in host memory."""
+
+    def __init__(self, L, shapes, storage):
+        self.L, self.keep = L, []
+        descs = (lbm.DomainDesc * len(shapes))()
+        for d, (nx, ny) in zip(descs, shapes):
+            a = (np.zeros((ny, nx), np.uint8), np.ones((ny, nx)), np.zeros((ny, nx)))
+            self.keep.append(a)
+            d.nx, d.ny = nx, ny
+            d.solid, d.rho_r0, d.rho_b0 = a[0].ctypes.data_as(C.POINTER(C.c_uint8)), lbm._ptr(a[1], C.c_double), lbm._ptr(a[2], C.c_double)
+            for k, v in W.free_droplet(n=8, radius=2.0).params.items():
+                setattr(d, k, float(v))
+        st, sc = C.c_size_t(), C.c_size_t()
+        self.ok(L.lbm_query_bytes(descs, len(descs), lbm.STORAGE[storage], C.byref(st), C.byref(sc)))
+        self.state, self.scratch = self.buffer(st.value), self.buffer(sc.value)
+        self.h = C.c_void_p()
+        self.ok(L.lbm_create(descs, len(descs), lbm.STORAGE[storage], self.state, st.value, self.scratch, sc.value, None,
+                             C.byref(self.h)))
+
+    def ok(self, rc):
+        assert rc == 0, self.L.lbm_last_error()
+
+    def buffer(self, n):
+        a = np.empty(n + 256, np.uint8)
+        self.keep.append(a)
+        return a.ctypes.data + -a.ctypes.data % 256
+
+    @property
+    def tile(self):
+        out = (C.c_int * 5)()
+        self.ok(self.L.lbm_get_tile(self.h, out))
+        return out[0], out[1], out[2], out[4]
+
+    def autotune(self, fast):
+        self.L.fast_shape(*fast)
+        out = (C.c_double * 5)()
+        self.ok(self.L.lbm_autotune(self.h, 1, self.buffer(self.L.lbm_state_size(self.h)), out))
+        assert self.tile == (out[0], out[1], out[2], out[4])
+        return self.tile
+
+    def __del__(self):
+        self.L.lbm_destroy(self.h)
+
+
+# heights at which the patch kernel's cut of the domains and the march's are the same list: 24 rows
+# against 16 (ny 9..16, 25..32) and 32 (ny 33..40, and 24 itself), 8 rows against 12 (ny <= 8)
+@pytest.mark.parametrize("storage,ny,fast", [("f32", 16, (24, 8, 1, 1)), ("f16", 9, (24, 8, 1, 1)), ("c16", 30, (24, 8, 1, 1)),
+                                             ("f32", 40, (32, 8, 1, 1)), ("f16", 24, (32, 8, 1, 1)), ("f32", 7, (12, 8, 1, 1)),
+                                             ("f64", 7, (12, 8, 1, 1)), ("f64", 100, (8, 8, 1, 1))])
+def test_autotune_tries_both_kernels_where_they_cut_alike(lib, storage, ny, fast):
+    assert Context(lib, [(60, ny), (112, ny)], storage).autotune(fast) == fast
