@@ -449,11 +449,27 @@ constexpr int DEFAULT_COLS = 1;
 //    storages only up to 16384 items: the gain is gone there; FP32 is bound by HBM.
 //  FP64: items of 8 rows up to 8192 (234 items 10.3 against 21.7, 4224 items 106 against 118,
 //    4800 items 122 against 123; 9600 items, 24 cylinder boxes, 226 against 201).
-constexpr size_t PATCH_ITEMS = 1408, PATCH_TALL_ITEMS_16 = 16384, PATCH_ITEMS_F64 = 8192;
+//  Lattices of 25 to 31 rows are two items of less than two thirds of the 24 rows; beyond 8192 such
+//    items the march, which takes each lattice in one item of a 4096 or more, is faster: 500 channels
+//    630 x 28 277 / 240 against 301 / 273 (FP32 / binary16, 12000 items), 270 of them 186 / 160
+//    against 171 / 146 (6480 items); 500 channels of 36 rows 351 / 290 against 341 / 305.
+constexpr size_t PATCH_ITEMS = 1408, PATCH_TALL_ITEMS_16 = 16384, PATCH_ITEMS_F64 = 8192, PATCH_HALF_ITEMS = 8192;
+bool half_empty(const std::vector<lbm_domain_desc> &d, const TileShape &tall, int storage) {
+    size_t items = 0, rows = 0;
+    for (const auto &q : d)
+        if (q.ny > PATCH_TALL_ROWS) {
+            const size_t s = (size_t)strips_of(q, tall, storage);
+            items += s * ((q.ny + PATCH_TALL_ROWS - 1) / PATCH_TALL_ROWS);
+            rows += s * q.ny;
+        }
+    return items > PATCH_HALF_ITEMS && 3 * rows < 2 * PATCH_TALL_ROWS * items;
+}
 TileShape builtin_tile(const std::vector<lbm_domain_desc> &d, int storage) {
     const TileShape patch{PATCH_ROWS, 8, 1, 1}, tall{PATCH_TALL_ROWS, 8, 1, 1};
     if (build_items(d, patch, storage).size() <= (storage == 0 ? PATCH_ITEMS_F64 : PATCH_ITEMS)) return patch;
-    if (storage == 1 || (storage > 1 && build_items(d, tall, storage).size() <= PATCH_TALL_ITEMS_16)) return tall;
+    if ((storage == 1 || (storage > 1 && build_items(d, tall, storage).size() <= PATCH_TALL_ITEMS_16)) &&
+        !half_empty(d, tall, storage))
+        return tall;
     TileShape t{0, DEFAULT_WAVES, DEFAULT_COLS, 1};
     t.chunk = auto_chunk(d, t, storage);
     return t;

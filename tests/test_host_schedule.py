@@ -133,3 +133,14 @@ class Context:
                                              ("f64", 7, (12, 8, 1, 1)), ("f64", 100, (8, 8, 1, 1))])
 def test_autotune_tries_both_kernels_where_they_cut_alike(lib, storage, ny, fast):
     assert Context(lib, [(60, ny), (112, ny)], storage).autotune(fast) == fast
+
+
+# (width, height, lattices): 4 columns are one strip
+@pytest.mark.parametrize("storage,batch,tile", [
+    ("f32", (4, 28, 4500), (64, 4, 1, 1)), ("f16", (4, 31, 4500), (64, 4, 1, 1)), ("c16", (4, 25, 4097), (64, 4, 1, 1)),
+    ("f32", (4, 28, 4096), (24, 8, 1, 1)), ("f16", (4, 32, 4500), (24, 8, 1, 1)), ("f32", (4, 10, 9000), (24, 8, 1, 1)),
+    ("f32", (4, 24, 9000), (24, 8, 1, 1))])
+def test_built_in_shape_of_half_empty_items(lib, storage, batch, tile):
+    """24-row items of lattices that leave a third of the rows empty, up to 8192 of them."""
+    nx, ny, n = batch
+    assert Context(lib, [(nx, ny)] * n, storage).tile == tile
