@@ -198,13 +198,17 @@ int64_t lbm_steps_taken(const lbm_ctx *ctx);
  *   cols 1, cols_per_lane 2: 128-column tiles with 116 output columns, each lane updating two
  *     adjacent nodes; only for the FP32-arithmetic storages and batches whose domains all have an
  *     even nx (never the built-in choice; lbm_autotune weighs it).
- * Blocks of 8 with one column and lane width 1 hold an item of 8 rows, or of 24 rows with FP32
- * arithmetic, as a whole instead of marching through it (56 output columns in every storage): the
- * built-in choice for small and medium batches.
- * 0 selects the built-in value.  Rebuilds the schedule.  Every shape computes the same method
- * with the same per-node arithmetic (FP64: the same bits; FP32 arithmetic: each shape is checked
- * against the FP64 oracle to the storage's rounding).  Synchronises the stream.  LBM_EINVAL for a
- * shape outside these. */
+ * waves 8, cols 1, cols_per_lane 1 hold an item of 8 rows, or of 24 rows with FP32 arithmetic, as a
+ * whole instead of marching through it (56 output columns in every storage).  That is the built-in
+ * choice for LBM_STORE_F64 up to 8192 items of 8 rows, for LBM_STORE_F32, and for the 16-bit storages
+ * up to 16384 items of 24 rows (in both, not for more than 8192 items of lattices of 25 to 31 rows,
+ * which leave them half empty).
+ * 0 selects the built-in value: in every argument (cols and cols_per_lane may be 1) the built-in
+ * shape of the batch; in one beside others that are given 4 wavefronts, 1 column and 1 column per
+ * lane, and for chunk_rows the height that suits the batch with them.
+ * Rebuilds the schedule.  Every shape computes the same method with the same per-node arithmetic
+ * (FP64: the same bits; FP32 arithmetic: each shape is checked against the FP64 oracle to the
+ * storage's rounding).  Synchronises the stream.  LBM_EINVAL for a shape outside these. */
 int lbm_set_tile(lbm_ctx *ctx, int chunk_rows, int waves, int cols, int cols_per_lane);
 
 /* The tile shape in use (the built-in choice, lbm_set_tile's or lbm_autotune's): shape_out

@@ -144,3 +144,12 @@ def test_built_in_shape_of_half_empty_items(lib, storage, batch, tile):
     """24-row items of lattices that leave a third of the rows empty, up to 8192 of them."""
     nx, ny, n = batch
     assert Context(lib, [(nx, ny)] * n, storage).tile == tile
+
+
+def test_zero_selects_the_built_in_value(lib):
+    c = Context(lib, [(60, 40)], "f32")
+    assert c.tile == (8, 8, 1, 1)  # one small lattice: 8-row items held whole
+    for given, want in (((8, 0, 0, 0), (8, 4, 1, 1)), ((24, 0, 0, 0), (24, 4, 1, 1)), ((0, 8, 0, 0), (8, 8, 1, 1)),
+                        ((0, 0, 2, 0), (8, 4, 2, 1)), ((0, 0, 0, 2), (8, 4, 1, 2)), ((0, 0, 1, 1), (8, 8, 1, 1))):
+        c.ok(lib.lbm_set_tile(c.h, *given))
+        assert c.tile == want, given
