@@ -60,8 +60,7 @@ struct Layout {
     size_t buf[2] = {0, 0}, f_bytes = 0, c_off = 0, vx_off = 0, vy_off = 0, hist[2] = {0, 0};
     size_t state_bytes = 0;
     // scratch
-    size_t mask = 0, ns = 0, inlet = 0, doms = 0, items = 0, partials = 0,
-           mass_out = 0, flag = 0, scratch_bytes = 0;
+    size_t mask = 0, ns = 0, inlet = 0, doms = 0, items = 0, partials = 0, flag = 0, scratch_bytes = 0;
 };
 
 int strips_of(const lbm_domain_desc &d, const TileShape &t, int storage) {
@@ -110,8 +109,6 @@ Layout make_layout(const lbm_domain_desc *d, int n, int storage) {
     o += align_up(cap * sizeof(WorkItem), 256);
     L.partials = o;
     o += align_up((size_t)n * L.bpd * 2 * sizeof(double), 256);
-    L.mass_out = o;
-    o += align_up((size_t)n * 2 * sizeof(double), 256);
     L.flag = o;
     o += 256;
     L.scratch_bytes = o;
