@@ -433,21 +433,27 @@ int auto_chunk(const std::vector<lbm_domain_desc> &d, TileShape t, int storage) 
 // every storage type.
 constexpr int DEFAULT_WAVES = 4;
 // One-wavefront tiles.  Tiles two wavefronts wide (120 output columns of 128; 118 with FP64
-// arithmetic) repeat fewer halo columns but measured 11 % slower on the sweep (1.75 against 1.57 ms
+// arithmetic) repeat fewer halo columns but measured 6 % slower on the sweep (1.67 against 1.57 ms
 // a step in binary16: 8-wavefront barriers, 2 blocks per CU).
 constexpr int DEFAULT_COLS = 1;
 // The built-in shape of a batch: the patch kernel, which takes a work item at once, while its
 // repeated halo rows cost less than the march's iterations (us per step on an MI355X, patch
 // against the best march):
-//  FP32 arithmetic, binary16 / FP32 storage: items of 8 rows up to 1408 of them (234 items 8.2
-//    against 20, 1404 items 20.4 against 33; 1600 items 23.4 where items of 24 rows take 19.9),
-//    then items of 24 rows: 44 channels 630 x 60 42 / 45 against 63, 16384 x 512 176 / 218 against
-//    186 / 250, 60 channels of the sweep (12240 items) 320 / 369 against 320 / 406.  In the 16-bit
-//    storages only up to 16384 items: the gain is gone there; FP32 is bound by HBM.
-//  FP64: items of 8 rows up to 8192 (234 items 10.3 against 21.7, 4224 items 106 against 118,
-//    4800 items 122 against 123; 9600 items, 24 cylinder boxes, 226 against 201).
+//  FP32 arithmetic: items of 8 rows up to 1408 of them, then of 24.  Above, 24 rows won wherever
+//    measured (15 channels 630 x 60, 1440 items of 8 rows, 20.8 / 22.4 against 22.7 / 22.5 in FP32 /
+//    binary16, four cylinder boxes 400 x 400, 1600 items, 18.7 / 19.9 against 23.7 / 23.5); from 1050
+//    on it depends on the lattices (12 channels 16.2 / 17.2 against 19.7 / 19.5, three boxes, 1200
+//    items, 19.4 / 19.8 against 19.0 / 18.4); 234 items take 8.2 with 8 rows, the march 20.
+//    Items of 24 rows against the march: 44 channels 42.5 / 42.5 against 63, 16384 x 512 218 / 176
+//    against 250 / 186, 60 channels of the sweep, 13212 items, 386 / 317 against 449 / 328.  FP32 stays
+//    ahead (150 of these channels 941 against 1056).  In the 16-bit storages up to 16384 items: 367
+//    against 373 at 15414 items, 495 against 488 at 20919.
+//  FP64: items of 8 rows up to 8192 (234 items 10.3 against 21.7, 4224 items 98 against 119, 8160
+//    items, 85 channels, 202 against 208, 8000 items, 20 cylinder boxes, 180 against 189; 9600
+//    items, 24 cylinder boxes, 213 against 201), with wetting variants likewise (4224 items 94
+//    against 119, 7800 items, 200 closed boxes, 207 against 220).
 //  Lattices of 25 to 31 rows are two items of less than two thirds of the 24 rows; beyond 8192 such
-//    items the march, which takes each lattice in one item of a 4096 or more, is faster: 500 channels
+//    items the march, which takes each lattice as one of more than 4096 items, is faster: 500 channels
 //    630 x 28 277 / 240 against 301 / 273 (FP32 / binary16, 12000 items), 270 of them 186 / 160
 //    against 171 / 146 (6480 items); 500 channels of 36 rows 351 / 290 against 341 / 305.
 constexpr size_t PATCH_ITEMS = 1408, PATCH_TALL_ITEMS_16 = 16384, PATCH_ITEMS_F64 = 8192, PATCH_HALF_ITEMS = 8192;

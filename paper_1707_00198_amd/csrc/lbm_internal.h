@@ -122,9 +122,10 @@ struct StepArgs {
 };
 
 // Launchers (lbm_kernels.hip).  storage: 0 f64, 1 f32, 2 f16, 3 c16.
-// waves x cols wavefronts per block: (4, 1), (8, 1) or (4, 2); a tile is 64 cols columns wide.
-// npl: node columns per lane, 1, or 2 (the pair kernel: FP32-arithmetic storages, cols = 1,
-// every domain of even width; the tile is then 128 columns wide).
+// Tile shape t: t.waves x t.cols wavefronts per block, (4, 1), (8, 1) or (4, 2); a tile is 64 t.cols
+// columns wide.  t.npl: node columns per lane, 1, or 2 (the pair kernel: FP32-arithmetic storages,
+// t.cols = 1, every domain of even width; the tile is then 128 columns wide).  t.patch(): the patch
+// kernel, in blocks of PATCH_WAVES wavefronts.
 // variants: some domain has nonzero wetting flags (selects the kernel that tests them).
 hipError_t launch_step(int storage, const void *args, int n_items, const TileShape &t, bool variants,
                        hipStream_t s);

@@ -30,9 +30,9 @@
 // Per-domain wetting variants of Sec. III A (scheme (b), Eq. 48; the surface-energy rule)
 // change stages B-E.
 //
-// Batches of few work items take a second form of the same step, patch_kernel: a short work item
-// held whole by a block of 16 wavefronts, each stage once.  All one-column forms share the node
-// arithmetic and give the same bits.  A diagnostic launch runs the same kernel without writing
+// All but large batches in the 16-bit and FP64 storages, and every FP32 one, take a second form of
+// the same step, patch_kernel: a short work item held whole by a block of 16 wavefronts, each stage
+// once.  All one-column forms share the node arithmetic and give the same bits.  A diagnostic launch runs the same kernel without writing
 // the state and outputs the velocity of Eq. 17 and, optionally, the contact-line nodes instead.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
@@ -66,9 +66,9 @@ __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x);
 __device__ __forceinline__ double fsqrt(double x) { return sqrt(x); }
 __device__ __forceinline__ float fsqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
 
-// a / b with ib within a few units of 1 / b, corrected by the residual: exactly 1 for a = b and free of the
-// reciprocal's systematic bias (the red fraction c = rho_R / rho must not drift the colour
-// masses); in FP64 the correctly rounded quotient but for rare last-bit cases.
+// a / b with ib within a few units of 1 / b, corrected by the residual: exactly 1 for a = b and
+// free of the reciprocal's systematic bias (the red fraction c = rho_R / rho must not drift the
+// colour masses); in FP64 the correctly rounded quotient but for rare last-bit cases.
 template <class AT>
 __device__ __forceinline__ AT quotient(AT a, AT b, AT ib) {
     const AT q = a * ib;
@@ -1223,7 +1223,7 @@ __global__ __launch_bounds__(TILE_LANES *R *C, march_occupancy(sizeof(typename C
 // One row per wavefront (8 output rows) gives the shortest time of one block, for small lattices;
 // two rows (24 output rows of 32; FP32 arithmetic) repeat fewer halo rows.  OCC = 8 wavefronts per
 // SIMD holds the kernel to 64 vector and 78 scalar registers, so that two blocks share a CU, one
-// loading while the other computes (44 channels of 630 x 60 in binary16: 45 us a step against 54).
+// loading while the other computes (44 channels of 630 x 60 in binary16: 42.5 us a step against 51.5).
 // What bounds it, on a 200 x 100 droplet (FP64, 52 blocks, 7.8 us a step; the march took 17): one
 // block's chain of loads, five stages and four barriers, and the 1.3 us between two launches; on
 // the 44 channels (42 us, 1.7 M nodes) the vector units and the waits of two blocks per CU.
@@ -1684,7 +1684,7 @@ __device__ __forceinline__ long long pull_elem(const Nbr &nb, int x, uint32_t m,
 constexpr int PAIR_HALO = 6;                          // halo columns per side (even)
 constexpr int PAIR_COLS = 2 * TILE_LANES;             // window columns
 constexpr int PAIR_OUT = PAIR_COLS - 2 * PAIR_HALO;   // output columns of a window
-static_assert(PAIR_OUT == 2 * TILE_LANES - 12, "the host's tile_out(cols, 2) strides strips by the pair window's outputs");
+static_assert(PAIR_OUT == 2 * TILE_LANES - 12, "TileShape::out strides the strips by the pair window's outputs");
 
 template <class T, int R, bool WV>
 __global__ __launch_bounds__(TILE_LANES *R, 2) void pair_kernel(const StepArgs<T, float> A) {
@@ -2386,8 +2386,9 @@ __global__ __launch_bounds__(CROSS_THREADS) void crossing_kernel(
 
 // ------------------------------------------------------------------- launchers
 // FP64 patches at 64 registers, two blocks on a CU, once there are more blocks than CUs; up to that
-// their few spilled registers only cost (200 x 100 droplet 8.04 against 8.34 us a step, 52 items;
-// 2000 x 100 channel, 468 items, 16.5 against 15.7, 44 channels, 4224 items, 123 against 110).
+// the bound only costs (200 x 100 droplet, 52 items, 7.86 us a step without it against 8.69, five
+// boxes, 195 items, 11.2 against 11.9; 2000 x 100 channel, 468 items, 15.9 against 14.2, 44
+// channels, 4224 items, 120 against 98).
 constexpr int PATCH64_ROOMY_ITEMS = 256;
 // Cache policy of the patch kernel's stores, by the bytes of the state (both copies) against the
 // 256 MB last-level cache.  While that holds the state, lines written through the L2 during the
@@ -2395,8 +2396,8 @@ constexpr int PATCH64_ROOMY_ITEMS = 256;
 // HBM one by one.  FP64 lines, seldom partial, are better streamed past the L2 once enough of the
 // state no longer fits.  The 16-bit storages gain nothing.  us per step on channels of 630 x 60
 // (MI355X), write-back / write-through / stream:
-//   FP64  45 MB 19.8 / 19.3 / 19.6, 180 MB 50.2 / 48.9 / 64.3, 270 MB 84.4 / 90.4 / 86.5,
-//         330 MB 106.5 / 113.7 / 102.1, 435 MB 137.7 / 147.9 / 132.9
+//   FP64  45 MB 19.1 / 19.0 / 18.7, 82 MB 28.0 / 27.7 / 30.2, 180 MB 48.6 / 48.1 / 63.1,
+//         270 MB 80.6 / 87.8 / 83.5, 330 MB 102.9 / 110.8 / 98.8, 435 MB 133.2 / 143.9 / 128.0
 //   FP32  82 MB 27.3 / 26.4 / 31.1, 165 MB 42.7 / 42.6 / 53.5, 247 MB 62.0 / 72.5 / 76.0,
 //         330 MB 98.6 / 111.2 / 98.0
 //   binary16  155 MB 58.8 / 59.0 / 69.4, 206 MB 73.9 / 74.6 / 88.4, 412 MB 168 / 191 / 172
