@@ -32,8 +32,9 @@
 //
 // All but large batches in the 16-bit and FP64 storages, and every FP32 one, take a second form of
 // the same step, patch_kernel: a short work item held whole by a block of 16 wavefronts, each stage
-// once.  All one-column forms share the node arithmetic and give the same bits.  A diagnostic launch runs the same kernel without writing
-// the state and outputs the velocity of Eq. 17 and, optionally, the contact-line nodes instead.
+// once.  All one-column forms share the node arithmetic and give the same bits.  A diagnostic
+// launch runs the same kernel without writing the state and outputs the velocity of Eq. 17 and,
+// optionally, the contact-line nodes instead.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
