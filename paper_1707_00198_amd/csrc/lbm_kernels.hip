@@ -411,17 +411,32 @@ __device__ __forceinline__ AT along(int a, AT vx, AT vy) {
 }
 
 // Adds the population f that direction a pulls from a node of colour state (c, v) to the red
-// density (c f + w_a e_a . v, Eq. 14; ev = e_a . v) and to the total.  The total takes the same
-// steps as the red density, so where every source is pure red (c = 1, v = 0) the two stay equal.
-// The sums run from the smallest populations to the largest (diagonal, axis, rest): the partial
-// sums, and with them the rounding errors of the colour split, then stay small for longest.
+// density (its red part is r = c f + w_a e_a . v, Eq. 14; ev = e_a . v) and to `rest`, of which
+// blue_of() then makes the blue density: rho_B is exactly 0 where every source is pure red (c = 1,
+// v = 0), and rho_R exactly 0 where every source is pure blue.  The sums run from the smallest
+// populations to the largest (diagonal, axis, rest): the partial sums, and with them the rounding
+// errors of the colour split, then stay small for longest.
+//  FP32: `rest` is the sum of the blue parts f - r, exact differences where the node is nearly red.
+//    As the total minus the red density, the blue in front of an interface would be the rounding of
+//    two sums of order one, which has a sign in this order: over 5000 steps of the sweep red then
+//    grew 2.0e-3 (binary16) and 1.2e-3 (c16) too slowly, 1.5e-4 and 0.9e-4 like this.
+//  FP64: `rest` is the total, which takes the same steps as the red density; one operation less.
 template <class AT>
-__device__ __forceinline__ void add_pull(int a, AT f, AT c, AT ev, AT &rR, AT &tot) {
+__device__ __forceinline__ void add_part(AT f, AT r, AT &rR, AT &rest) {
+#pragma clang fp contract(on)
+    rR = rR + r;
+    rest = rest + (sizeof(AT) == 4 ? f - r : f);
+}
+template <class AT>
+__device__ __forceinline__ void add_pull(int a, AT f, AT c, AT ev, AT &rR, AT &rest) {
 #pragma clang fp contract(on)
     const AT p = wgt<AT>(a) * ev;
     const AT r = c * f + p;
-    rR = rR + r;
-    tot = tot + f;
+    add_part(f, r, rR, rest);
+}
+template <class AT>
+__device__ __forceinline__ AT blue_of(AT rR, AT rest) {
+    return sizeof(AT) == 4 ? rest : rest - rR;
 }
 __device__ constexpr int PULL_ORDER[8] = {5, 6, 7, 8, 1, 2, 3, 4};
 
@@ -429,24 +444,23 @@ __device__ constexpr int PULL_ORDER[8] = {5, 6, 7, 8, 1, 2, 3, 4};
 template <class AT, class ColourFn>
 __device__ __forceinline__ void gather_interior(ParC<AT> &P, const AT d[9], AT cself, AT &rR, AT &rB, ColourFn colour) {
 #pragma clang fp contract(on)
-    AT tot = AT(0), c, ev;
+    AT rest = AT(0), c, ev;
     rR = AT(0);
 #pragma unroll
     for (int k = 0; k < 8; k++) {
         const int a = PULL_ORDER[k];
         colour(a, false, c, ev);
-        add_pull(a, (a < 5 ? P.w_axis : P.w_diag) + d[a], c, ev, rR, tot);
+        add_pull(a, (a < 5 ? P.w_axis : P.w_diag) + d[a], c, ev, rR, rest);
         // FP64: the total's first half before the red density's second.  Left to itself the compiler
         // sums the total last, from eight populations kept until then, and the 64-register patches
         // spill 6 of them (44 channels of 630 x 60: 113 us a step against 98; a tie after every
         // second pull 98, after the last 103.5).
-        if (sizeof(AT) == 8 && k == 3) asm("" : "+v"(rR), "+v"(tot));
+        if (sizeof(AT) == 8 && k == 3) asm("" : "+v"(rR), "+v"(rest));
     }
     const AT f0 = P.w_rest + d[0];
     const AT r0 = cself * f0;
-    rR = rR + r0;
-    tot = tot + f0;
-    rB = tot - rR;
+    add_part(f0, r0, rR, rest);
+    rB = blue_of(rR, rest);
 }
 
 // Completes the post-streaming populations d[] of fluid node (x, y) whose interior pulls are
@@ -517,9 +531,7 @@ __device__ __forceinline__ void finish_gather(const StepArgs<T, AT> &A, DomC &D,
                 d[a] = v;
             }
         }
-        // rho_B as the total minus rho_R: exactly 0 where every source is pure red (c = 1,
-        // v = 0), and rho_R exactly 0 where every source is pure blue
-        AT tot = AT(0);
+        AT rest = AT(0);
 #pragma unroll
         for (int k = 0; k < 8; k++) {
             const int a = PULL_ORDER[k];
@@ -529,13 +541,12 @@ __device__ __forceinline__ void finish_gather(const StepArgs<T, AT> &A, DomC &D,
             // across the inlet: pure red; across the outlet: the node's red fraction
             c = outside ? (EX[a] > 0 ? AT(1) : cself) : c;
             ev = outside ? AT(0) : ev;
-            add_pull(a, wr[a < 5 ? 1 : 2] + d[a], c, ev, rR, tot);
+            add_pull(a, wr[a < 5 ? 1 : 2] + d[a], c, ev, rR, rest);
         }
         const AT f0 = wr[0] + d[0];
         const AT r0 = cself * f0;
-        rR = rR + r0;
-        tot = tot + f0;
-        rB = tot - rR;
+        add_part(f0, r0, rR, rest);
+        rB = blue_of(rR, rest);
     }
     if (write_hist && nb.hi) {
         AT *h = A.hist_out + (D.io_off + y) * 3;

@@ -62,6 +62,14 @@ template <class AT> static void nodes(const Q *q, int n, const AT *d, int red, A
 extern "C" {
 void nodes_f64(const Q *q, int n, const double *d, int red, double *o, double *u) { nodes(q, n, d, red, o, u); }
 void nodes_f32(const Q *q, int n, const float *d, int red, float *o, float *u) { nodes(q, n, d, red, o, u); }
+// densities of n interior nodes from the deviations d, the red fractions c and e_a . v of their sources
+void gather_f32(const Q *q, int n, const float *d, const float *c, const float *ev, float *rho) {
+    DomDev D{};
+    fill(*q, D);
+    for (int i = 0; i < n; i++)
+        gather_interior(of(D, 0.0f), d + 9 * i, c[9 * i], rho[2 * i], rho[2 * i + 1],
+                        [&](int a, bool, float &cs, float &e) { cs = c[9 * i + a]; e = ev[9 * i + a]; });
+}
 void normals_f64(int n, const double *g, double eps, double *out) {
     for (int i = 0; i < n; i++) unit_normal(g[2 * i], g[2 * i + 1], eps, out[3 * i], out[3 * i + 1], out[3 * i + 2]);
 }
@@ -185,3 +193,27 @@ def test_fp32_normals(lib):
     assert not r.any()
     lib.normals_f32(n, p(g), C.c_float(1e-30), p(r))
     assert np.isfinite(r).all() and np.abs(r[:, 1:]).max() <= 1.0 + 2.0 ** -22
+
+
+def test_fp32_densities_of_the_minority_colour(lib):
+    """The blue density of nearly red nodes carries the rounding of each red part alone: half a unit
+    of populations near 4/9 (2^-26), 1/9 (2^-28) and 1/36 (2^-30), 1.125 x 2^-25 over the nine (the
+    parts' own sums are a thousand times smaller), where the total minus the red density would add
+    the roundings of two sums of order one.  Pure nodes are exactly pure."""
+    rng = np.random.default_rng(7)
+    n = 20000
+    p = lambda a: a.ctypes.data_as(C.c_void_p)  # noqa: E731
+    w = np.array([4 / 9] + [1 / 9] * 4 + [1 / 36] * 4, np.float32)
+    d = (rng.uniform(-0.02, 0.02, (n, 9)) * w).astype(np.float32)
+    c = (1.0 - 10.0 ** rng.uniform(-7.0, -3.0, (n, 9))).astype(np.float32)
+    ev = ((1 - c) * rng.uniform(-0.5, 0.5, (n, 9))).astype(np.float32)
+    ev[:, 0] = 0
+    rho = np.empty((n, 2), np.float32)
+    lib.gather_f32(C.byref(_params(0.5, 0.25)), n, p(d), p(c), p(ev), p(rho))
+    f, ld = (w + d).astype(np.longdouble), np.longdouble
+    want = ((1 - c.astype(ld)) * f - w.astype(ld) * ev).sum(axis=1)
+    assert np.abs(rho[:, 1] - want).max() <= 1.125 * 2.0 ** -25 + 9 * 2.0 ** -34
+    for pure in (0, 1):
+        c[:], ev[:] = pure, 0
+        lib.gather_f32(C.byref(_params(0.5, 0.25)), n, p(d), p(c), p(ev), p(rho))
+        assert (rho[:, 1 - pure] > 0).all() and not rho[:, pure].any()
