@@ -480,7 +480,7 @@ TileShape builtin_tile(const std::vector<lbm_domain_desc> &d, int storage) {
 // The pair kernel (two node columns per lane) needs FP32 arithmetic and an even width in every
 // domain.  It is offered to lbm_set_tile and the autotuner but is not the built-in choice: at the
 // two wavefronts per SIMD its register use allows, it measured slower than the one-column kernel
-// at five (binary16 sweep 45.9 against 52.6 GLUPS).
+// at five (binary16 sweep 45.6 against 52.4 GLUPS).
 bool pair_allowed(int storage, const std::vector<lbm_domain_desc> &d) {
     if (storage == 0) return false;
     for (const auto &q : d)
